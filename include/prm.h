@@ -187,8 +187,8 @@ int prm_plan_workspace_bytes(int32_t n_mats, const int64_t* rows, const int64_t*
  * 2 x the multiply-adds of the product a launch forms, per matrix: 2r^2c
  * (Gram, apply: r x r times r x c), 2r^3 (square, and the r x r split
  * products of the factored form).  Executed FLOPs are what the matrix cores
- * actually run: padded 256 x 256 tiles, only the upper tiles of symmetric
- * results, and the diagonal-term MFMAs of the apply. */
+ * actually run: padded tiles, only the upper tiles of symmetric results, and
+ * the diagonal-term MFMAs of the large-tile apply. */
 #define PRM_NUM_KERNEL_CLASSES 11
 typedef struct prm_kernel_stats {
   char name[32];
@@ -300,7 +300,7 @@ int prm_peak_hbm(void* hip_stream, uint64_t bytes, double* read_gbs, double* wri
  * step that needs more is refused with PRM_ENOMEM before anything is enqueued
  * (a refresh step needs 4 rp cp + 8 rp^2 bytes in the factored form, c >= 2r,
  * and 4 rp cp + 4 rp^2 otherwise, with rp x cp the oriented shape padded to
- * 256: 3072 x 12288 and 5120 x 5120 fit, 3072 x 18432 does not; row-wise steps of wide
+ * 256 (whatever the tile it runs on): 3072 x 12288 and 5120 x 5120 fit, 3072 x 18432 does not; row-wise steps of wide
  * matrices need no workspace).  Every call on one GPU uses the same array:
  * calls that overlap in time on one GPU (on other streams or threads) RACE
  * and give wrong results; calls ordered on one stream are safe, and every byte

@@ -241,6 +241,7 @@ __global__ __launch_bounds__(gemm::NTHREADS, 1) void ns_gemm_kernel(const MatDes
   __shared__ __attribute__((aligned(16))) char s1[STAGE_BYTES];
 
   const Item it = items[blockIdx.x];
+  if (it.mat < 0) return;  // filler of the XCD-interleaved order (whole work group)
   const MatDesc& d = md[it.mat];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

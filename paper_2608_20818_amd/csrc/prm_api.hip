@@ -111,6 +111,7 @@ struct NsGroup {
   std::vector<int32_t> mats;
   std::vector<Item> upper, apply;
   size_t off_upper = 0, off_apply = 0;
+  int32_t n_upper = 0, n_apply = 0;  // work groups of a launch (list lengths)
   double elems = 0, alg_rc = 0, alg_rr = 0, exec_gram = 0, exec_rr = 0, exec_apply = 0;
 };
 
@@ -126,6 +127,7 @@ struct Plan {
   int32_t n = 0;
   std::vector<int64_t> m, nn, rp, cp;
   std::vector<int32_t> tall;
+  int32_t tile = kNsTile;           // tile edge of the NS5 products: 64, 128 (ns5_small.hip) or 256 (ns5.hip)
   std::vector<int32_t> chain;       // NS5 in the factored form (oriented c >= 2r)
   int32_t precise = 0;              // every iterate carried as hi + lo bf16 (plain path)
   std::vector<float> s;
@@ -182,10 +184,21 @@ float shape_scale(int64_t m, int64_t n, int mode) {
 // (A, B), four on the factored one.
 int ns_splits(int chain) { return chain ? 4 : 2; }
 int ns_iterates(int precise) { return precise ? 4 : 2; }
+// Regions are sized for the shape padded to kNsTile whatever tile the plan runs
+// on, so that what a context allocates, and what a workspace budget or the
+// scratch array of the allocation-free step admits, does not depend on it.
+struct NsRegions {
+  uint64_t iterate, split, diag;  // bytes of one iterate, split matrix and diagonal
+  NsRegions(int64_t rp, int64_t cp) {
+    const uint64_t r = (uint64_t)round_up(rp, kNsTile), c = (uint64_t)round_up(cp, kNsTile);
+    iterate = align256(r * c * 2);
+    split = align256(r * r * 2);
+    diag = align256(r * 4);
+  }
+};
 uint64_t ns_matrix_bytes(int64_t rp, int64_t cp, int chain, int precise) {
-  const uint64_t xs = align256((uint64_t)rp * cp * 2), gs = align256((uint64_t)rp * rp * 2),
-                 vs = align256((uint64_t)rp * 4);
-  return (uint64_t)ns_iterates(precise) * xs + (uint64_t)ns_splits(chain) * (gs + vs);
+  const NsRegions g(rp, cp);
+  return (uint64_t)ns_iterates(precise) * g.iterate + (uint64_t)ns_splits(chain) * (g.split + g.diag);
 }
 
 // Row-wise launch class of a wide row of length n (0 tpr = generic path).
@@ -199,8 +212,50 @@ void wide_class(int64_t n, int& tpr, int& nch) {
   else if (chunks <= 512 * 8) { tpr = 512; nch = (int)((chunks + 511) / 512); }
 }
 
+// Tile edge of the plan's NS5 products: 256 runs its MFMAs best, smaller tiles
+// spread a small set over more CUs and pad less.  Each product is priced as if
+// every matrix ran in one launch over the chip's 256 CUs: all tiles' time over
+// 256 plus half the longest tile (the uneven end), but no less than the longest.
+// A tile costs its K / 64 stages plus a fixed part, in us as measured (a stage
+// of 64 moves 16, 32 or 64 KB into LDS, at 31 to 39 bytes per clock and CU).
+// Measured refresh, us at 64 / 128 / 256, the choice first: six matrices with
+// r <= 256: 100 / 153 / 580; ten with r = 384 (three steps): 294 / 322 / 980;
+// seven with r <= 1001: 128: 550, 559 / 1500; five with r = 1024, precise: 128:
+// 1168, 1410 / 2430; one 2048 x 6144: 128: 522, 667 / 1060; 15 with r = 2048:
+// 256: 5700, 8831 / 6695.
+void choose_tile(Plan& P) {
+  struct Price { int tile; double stage, fixed; };
+  constexpr Price price[3] = {{256, 1.17, 9.0}, {128, 0.42, 5.0}, {64, 0.16, 3.5}};
+  constexpr double kCus = 256;
+  double best = 0;
+  for (const Price& pr : price) {
+    // Gram, r x r products, apply: time of all tiles, of the longest, launches
+    // over the set (mean; the factored form runs 2, 14, 2, the plain one 5 each)
+    double total[3] = {0, 0, 0}, longest[3] = {0, 0, 0}, count[3] = {0, 0, 0}, est = 0;
+    for (int i = 0; i < P.n; ++i) {
+      const double r = (double)round_up(std::min(P.m[i], P.nn[i]), pr.tile);
+      const double c = (double)round_up(std::max(P.m[i], P.nn[i]), pr.tile);
+      const double tr = r / pr.tile, tc = c / pr.tile;
+      const double time[3] = {c / 64 * (P.precise ? 3 : 1) * pr.stage + pr.fixed, r / 64 * pr.stage + pr.fixed,
+                              r / 64 * (P.precise ? 2 : 1) * pr.stage + pr.fixed};
+      const double tiles[3] = {tr * (tr + 1) / 2, tr * (tr + 1) / 2, tr * tc};
+      for (int k = 0; k < 3; ++k) {
+        total[k] += tiles[k] * time[k];
+        longest[k] = std::max(longest[k], time[k]);
+        count[k] += (P.chain[i] ? (k == 1 ? 14.0 : 2.0) : 5.0) / P.n;
+      }
+    }
+    for (int k = 0; k < 3; ++k) est += count[k] * std::max(longest[k], total[k] / kCus + 0.5 * longest[k]);
+    if (pr.tile == 256 || est < best) {
+      best = est;
+      P.tile = pr.tile;
+    }
+  }
+}
+
+// `tile`: the tile edge to plan for, 0 for choose_tile's.
 int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const prm_config* cfg,
-              Plan& P) {
+              Plan& P, int tile = 0) {
   int rc = validate_cfg(cfg);
   if (rc) return rc;
   if (n_mats < 0) return fail(PRM_EINVAL, "n_mats must be >= 0");
@@ -220,15 +275,19 @@ int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const pr
     // rounding stays below the plain path's only away from square shapes;
     // precise mode runs the plain path
     P.chain.push_back(!cfg->ns_plain && !cfg->ns_precise && c >= 2 * r ? 1 : 0);
-    P.rp.push_back(round_up(r, kNsTile));
-    P.cp.push_back(round_up(c, kNsTile));
     P.s.push_back(shape_scale(m, n, cfg->scale_mode));
+  }
+  if (tile) P.tile = tile;
+  else choose_tile(P);
+  for (int i = 0; i < n_mats; ++i) {
+    P.rp.push_back(round_up(std::min(P.m[i], P.nn[i]), P.tile));
+    P.cp.push_back(round_up(std::max(P.m[i], P.nn[i]), P.tile));
   }
   // ---- small persistent buffers: prologue partial sums + alpha per matrix ----
   uint64_t off = 0;
   P.small_off.resize(n_mats);
   for (int i = 0; i < n_mats; ++i) {
-    const int64_t pt = (P.rp[i] / kPrologueTile) * (P.cp[i] / kPrologueTile);
+    const int64_t pt = (round_up(P.rp[i], kNsTile) / kPrologueTile) * (round_up(P.cp[i], kNsTile) / kPrologueTile);
     P.small_off[i] = off;
     off = align256(off + (uint64_t)(pt + 1) * 4);
   }
@@ -250,8 +309,9 @@ int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const pr
   std::vector<int32_t> order(n_mats);
   for (int i = 0; i < n_mats; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-    if (P.rp[a] != P.rp[b]) return P.rp[a] > P.rp[b];
-    return P.cp[a] > P.cp[b];
+    const int64_t ra = round_up(P.rp[a], kNsTile), rb = round_up(P.rp[b], kNsTile);
+    if (ra != rb) return ra > rb;
+    return round_up(P.cp[a], kNsTile) > round_up(P.cp[b], kNsTile);
   });
   P.ws_off.assign(n_mats, 0);
   uint64_t cur = 0;
@@ -274,11 +334,11 @@ int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const pr
 }
 
 // Work groups are dispatched round-robin over the eight XCDs (group b runs on
-// XCD b mod 8), and each XCD has its own L2.  A GEMM work list therefore keeps
-// all tiles of one matrix on one XCD (matrix k of the chunk -> XCD k mod 8) and
-// orders them in super-rows of kSuperRows tile rows, so that the ~32 groups an
-// XCD runs at once share a few row and column panels of the operands.  The
-// per-XCD lists are then interleaved into one launch order.
+// XCD b mod 8), and each XCD has its own L2.  A GEMM work list orders the tiles
+// of a matrix in super-rows of kSuperRows tile rows, so that the groups an XCD
+// runs at once share a few row and column panels of the operands, deals whole
+// pieces of that order to the XCDs (XcdLists), and interleaves the XCDs' lists
+// into one launch order.
 constexpr int kXcds = 8;
 constexpr int kSuperRows = 4;
 
@@ -293,20 +353,54 @@ void tile_order(int32_t mat, int32_t tr, int32_t tc, bool upper, std::vector<Ite
   }
 }
 
-// Interleave per-XCD item lists so that list x lands on positions = x mod 8
-// while every list still has items.
-std::vector<Item> interleave_xcd(const std::vector<std::vector<Item>>& per) {
-  std::vector<Item> out;
-  size_t total = 0;
-  for (const auto& v : per) total += v.size();
-  out.reserve(total);
-  std::vector<size_t> pos(per.size(), 0);
-  while (out.size() < total) {
-    for (size_t x = 0; x < per.size(); ++x)
-      if (pos[x] < per[x].size()) out.push_back(per[x][pos[x]++]);
+// Tiles of several matrices dealt to the XCDs.  Each matrix's tile order is cut
+// into `pieces` runs; a run goes to the XCD with the least work so far (a tile's
+// work is its K).  If whole matrices (or the given runs) leave the fullest XCD
+// more than 3% above the mean, the runs are halved: a set of 12 equal matrices
+// would give four XCDs twice the tiles of the others.  The launch order puts
+// XCD x's list on positions = x mod 8, with fillers (mat = -1) where it is
+// shorter than the others.
+struct XcdLists {
+  std::vector<std::vector<Item>> mats;
+  std::vector<double> weight;
+  int pieces;
+  explicit XcdLists(int first_pieces) : pieces(first_pieces) {}
+  void add(const std::vector<Item>& tiles, double k) {
+    mats.push_back(tiles);
+    weight.push_back(k);
   }
-  return out;
-}
+  std::vector<Item> interleaved() const {
+    size_t most = 0;
+    for (const auto& t : mats) most = std::max(most, t.size());
+    std::vector<std::vector<Item>> per;
+    for (size_t d = pieces;; d *= 2) {
+      per.assign(kXcds, {});
+      std::vector<double> load(kXcds, 0.0);
+      for (size_t i = 0; i < mats.size(); ++i) {
+        const size_t n = mats[i].size();
+        for (size_t k = 0; k < d; ++k) {
+          const size_t lo = n * k / d, hi = n * (k + 1) / d;
+          if (lo == hi) continue;
+          const size_t x = std::min_element(load.begin(), load.end()) - load.begin();
+          per[x].insert(per[x].end(), mats[i].begin() + lo, mats[i].begin() + hi);
+          load[x] += weight[i] * (double)(hi - lo);
+        }
+      }
+      double sum = 0, top = 0;
+      for (double v : load) {
+        sum += v;
+        top = std::max(top, v);
+      }
+      if (top <= 1.03 * sum / kXcds || d >= most) break;
+    }
+    size_t len = 0;
+    for (const auto& v : per) len = std::max(len, v.size());
+    std::vector<Item> out(len * kXcds, Item{-1, 0, 0, 0});
+    for (int x = 0; x < kXcds; ++x)
+      for (size_t k = 0; k < per[x].size(); ++k) out[k * kXcds + x] = per[x][k];
+    return out;
+  }
+};
 
 // Work lists (host side); built only by prm_init.
 void build_lists(Plan& P, const prm_config* cfg) {
@@ -356,35 +450,39 @@ void build_lists(Plan& P, const prm_config* cfg) {
     }
     for (int grp = 0; grp < 2; ++grp) {
       NsGroup& G = grp ? ch.chain : ch.plain;
-      std::vector<std::vector<Item>> u(kXcds), a(kXcds);
+      // symmetric products: whole matrices per XCD where that balances (their
+      // tiles share the r x r panels in the XCD's L2).  Apply: an eighth of each
+      // matrix per XCD, so all XCDs stream the same factor at the same time (it
+      // is read by every tile row; the last-level cache serves the repeats).
+      XcdLists u(1), a(kXcds);
+      std::vector<Item> tiles;
       for (int i : ch.mats) {
         if (P.chain[i] != grp) continue;
-        const size_t k = G.mats.size();
         G.mats.push_back(i);
         const double r = (double)std::min(P.m[i], P.nn[i]), c = (double)std::max(P.m[i], P.nn[i]);
-        const double rp = (double)P.rp[i], cp = (double)P.cp[i], t2 = (double)kNsTile * kNsTile;
-        const int32_t tr = (int32_t)(P.rp[i] / kNsTile), tc = (int32_t)(P.cp[i] / kNsTile);
+        const double rp = (double)P.rp[i], cp = (double)P.cp[i];
+        const double t2 = (double)P.tile * P.tile;
+        const int32_t tr = (int32_t)(P.rp[i] / P.tile), tc = (int32_t)(P.cp[i] / P.tile);
         const double upper = (double)tr * (tr + 1) / 2;
         G.elems += r * c;
         G.alg_rc += 2 * r * r * c;
         G.alg_rr += 2 * r * r * r;
         G.exec_gram += upper * 2 * t2 * cp;
         G.exec_rr += upper * 2 * t2 * rp;
-        // the apply's diagonal term adds 64 MFMAs per wave to 64 per stage
-        G.exec_apply += (double)tc * tr * 2 * t2 * rp * (1.0 + kNsTile / 4.0 / rp);
-        // symmetric products: each matrix's (upper) tiles stay on one XCD,
-        // whose 32 CUs then share its r x r panels in their L2
-        tile_order(i, tr, tr, true, u[k % kXcds]);
-        // apply: every XCD takes a contiguous eighth of each matrix's tile
-        // order, so all XCDs stream the same factor at the same time (it is
-        // read by every tile row; the last-level cache serves the repeats)
-        std::vector<Item> ta;
-        tile_order(i, tc, tr, false, ta);  // tiles of X'^T: rows over c, columns over r
-        for (int x = 0; x < kXcds; ++x)
-          a[x].insert(a[x].end(), ta.begin() + ta.size() * x / kXcds, ta.begin() + ta.size() * (x + 1) / kXcds);
+        // the large-tile apply's diagonal term adds 64 MFMAs per wave to 64 per stage
+        G.exec_apply += (double)tc * tr * 2 * t2 * rp * (P.tile == kNsTile ? 1.0 + kNsTile / 4.0 / rp : 1.0);
+        tiles.clear();
+        tile_order(i, tr, tr, true, tiles);
+        u.add(tiles, cp);
+        // tiles of X'^T: rows over c, columns over r
+        tiles.clear();
+        tile_order(i, tc, tr, false, tiles);
+        a.add(tiles, rp);
       }
-      G.upper = interleave_xcd(u);
-      G.apply = interleave_xcd(a);
+      G.upper = u.interleaved();
+      G.apply = a.interleaved();
+      G.n_upper = (int32_t)G.upper.size();
+      G.n_apply = (int32_t)G.apply.size();
     }
   }
   (void)cfg;
@@ -433,8 +531,8 @@ void fill_descs(const Plan& P, char* chunk_base, char* small_base, char* tall_ba
     d.tall = P.tall[i];
     d.rp = P.rp[i];
     d.cp = P.cp[i];
-    const uint64_t xs = align256((uint64_t)d.rp * d.cp * 2), gs = align256((uint64_t)d.rp * d.rp * 2),
-                   vs = align256((uint64_t)d.rp * 4);
+    const NsRegions g(d.rp, d.cp);
+    const uint64_t xs = g.iterate, gs = g.split, vs = g.diag;
     char* w = chunk_base + P.ws_off[i];
     const int nx = ns_iterates(P.precise);
     d.XT = (uint16_t*)w;
@@ -611,6 +709,57 @@ int rowwise_step(prm_ctx* c, float lr, bool debug) {
   return PRM_OK;
 }
 
+// One product of the NS5 sequence of a group: Gram of the iterate `src` into
+// S[so]; B = bA + cA^2 from S[sx] into S[so]; the split product (S[sx] + xs I)
+// (S[sy] + ys I) into S[so]; the apply of (S[sy] + ys I) to the iterate `src`,
+// into the other iterate or, `last`, into W.
+struct NsLaunch {
+  const NsGroup* G;
+  NsOp op;
+};
+
+NsLaunch op_gram(const NsGroup& G, int src, int alpha, int so) {
+  return {&G, NsOp{GEMM_GRAM, src, alpha, 0, 0, 0, so, 0.f, 0.f}};
+}
+NsLaunch op_poly(const NsGroup& G, int sx, int so) {
+  return {&G, NsOp{GEMM_POLY, 0, 0, 0, sx, sx, so, 0.f, 0.f}};
+}
+NsLaunch op_sprod(const NsGroup& G, int sx, float xs, int sy, float ys, int so) {
+  return {&G, NsOp{GEMM_SPROD, 0, 0, 0, sx, sy, so, xs, ys}};
+}
+NsLaunch op_apply(const NsGroup& G, int src, int alpha, int sy, float ys, int last) {
+  return {&G, NsOp{GEMM_APPLY, src, alpha, last, 0, sy, 0, 0.f, ys}};
+}
+
+// eq. (app-ns-recurrence) as written: A_j = X_j X_j^T in S0, B_j in S1,
+// X_{j+1} = (aI + B_j) X_j
+std::vector<NsLaunch> plain_sequence(const NsGroup& G, float a) {
+  std::vector<NsLaunch> v;
+  for (int j = 0; j < 5; ++j) {
+    v.push_back(op_gram(G, j & 1, j == 0, 0));
+    v.push_back(op_poly(G, 0, 1));
+    v.push_back(op_apply(G, j & 1, j == 0, 1, a, j == 4));
+  }
+  return v;
+}
+
+// the factored form, with P_j = aI + B_j:
+//   j = 0: A0 (S0) = X0 X0^T, B0 (S1)
+//   j = 1: P0^2 (S2), A1 = P0^2 A0 (S3), B1 (S0), Q = P1 P0 (S2); X2 = Q X0
+//   j = 2: A2 (S0) = X2 X2^T, B2 (S1)
+//   j = 3: P2^2 (S2), A3 = P2^2 A2 (S3), B3 (S0), Q = P3 P2 (S2)
+//   j = 4: P3^2 (S1), A4 = P3^2 A3 (S0), B4 (S1), Q = P4 Q (S3); X5 = Q X2
+std::vector<NsLaunch> chain_sequence(const NsGroup& G, float a) {
+  return {op_gram(G, 0, 1, 0),           op_poly(G, 0, 1),
+          op_sprod(G, 1, a, 1, a, 2),    op_sprod(G, 2, 0.f, 0, 0.f, 3), op_poly(G, 3, 0),
+          op_sprod(G, 0, a, 1, a, 2),    op_apply(G, 0, 1, 2, 0.f, 0),
+          op_gram(G, 1, 0, 0),           op_poly(G, 0, 1),
+          op_sprod(G, 1, a, 1, a, 2),    op_sprod(G, 2, 0.f, 0, 0.f, 3), op_poly(G, 3, 0),
+          op_sprod(G, 0, a, 1, a, 2),
+          op_sprod(G, 0, a, 0, a, 1),    op_sprod(G, 1, 0.f, 3, 0.f, 0), op_poly(G, 0, 1),
+          op_sprod(G, 1, a, 2, 0.f, 3),  op_apply(G, 1, 0, 3, 0.f, 1)};
+}
+
 int refresh_step(prm_ctx* c, float lr, bool debug) {
   const Plan& P = c->plan;
   const prm_config& cf = c->cfg;
@@ -643,66 +792,51 @@ int refresh_step(prm_ctx* c, float lr, bool debug) {
       return launch_ns_alpha(md, c->d_ints + ch.off_mats, (int32_t)ch.mats.size(), p, c->stream);
     });
     if (rc) return rc;
-    for (const NsGroup* Gp : {&ch.plain, &ch.chain}) {
-      const NsGroup& G = *Gp;
-      if (G.mats.empty()) continue;
-      const Item* upper = c->d_items + G.off_upper;
-      const Item* apply = c->d_items + G.off_apply;
-      const int32_t nu = (int32_t)G.upper.size(), na = (int32_t)G.apply.size();
-      // one kernel of the sequence: Gram of the iterate `src` into S[so];
-      // B = bA + cA^2 from S[sx] into S[so]; the split product
-      // (S[sx] + xs I)(S[sy] + ys I) into S[so]; the apply of (S[sy] + ys I)
-      // to the iterate `src`, into the other iterate or, `last`, into W
-      auto gram = [&](int src, int alpha, int so) {
-        p.src = src; p.use_alpha = alpha; p.so = so;
-        return timed(c, K_NS_GRAM, 0, G.alg_rc, [&] {
-          return launch_ns_gemm(GEMM_GRAM, wt, md, upper, nu, p, c->stream, hilo);
-        }, G.exec_gram * (hilo ? 3 : 1));
-      };
-      auto poly = [&](int sx, int so) {
-        p.sx = sx; p.sy = sx; p.so = so; p.xshift = 0.f; p.yshift = 0.f;
-        return timed(c, K_NS_POLY, 0, G.alg_rr, [&] {
-          return launch_ns_gemm(GEMM_POLY, wt, md, upper, nu, p, c->stream);
-        }, G.exec_rr);
-      };
-      auto sprod = [&](int sx, float xs, int sy, float ys, int so) {
-        p.sx = sx; p.sy = sy; p.so = so; p.xshift = xs; p.yshift = ys;
-        return timed(c, K_NS_SPROD, 0, G.alg_rr, [&] {
-          return launch_ns_gemm(GEMM_SPROD, wt, md, upper, nu, p, c->stream);
-        }, G.exec_rr);
-      };
-      auto applyk = [&](int src, int alpha, int sy, float ys, int last) {
-        p.src = src; p.use_alpha = alpha; p.sy = sy; p.yshift = ys; p.last = last;
-        rc = timed(c, K_NS_APPLY, last ? G.elems * (2 * wb + db) : 0, G.alg_rc, [&] {
-          return launch_ns_gemm(GEMM_APPLY, wt, md, apply, na, p, c->stream, hilo);
-        }, G.exec_apply * (hilo ? 2 : 1));
-        p.last = 0;
-        return rc;
-      };
-      if (Gp == &ch.plain) {
-        // eq. (app-ns-recurrence) as written: A_j = X_j X_j^T in S0, B_j in S1,
-        // X_{j+1} = (aI + B_j) X_j
-        for (int j = 0; j < 5; ++j) {
-          if ((rc = gram(j & 1, j == 0, 0)) || (rc = poly(0, 1)) || (rc = applyk(j & 1, j == 0, 1, a, j == 4)))
-            return rc;
-        }
-      } else {
-        // the factored form, with P_j = aI + B_j:
-        //   j = 0: A0 (S0) = X0 X0^T, B0 (S1)
-        //   j = 1: P0^2 (S2), A1 = P0^2 A0 (S3), B1 (S0), Q = P1 P0 (S2); X2 = Q X0
-        //   j = 2: A2 (S0) = X2 X2^T, B2 (S1)
-        //   j = 3: P2^2 (S2), A3 = P2^2 A2 (S3), B3 (S0), Q = P3 P2 (S2)
-        //   j = 4: P3^2 (S1), A4 = P3^2 A3 (S0), B4 (S1), Q = P4 Q (S3); X5 = Q X2
-        if ((rc = gram(0, 1, 0)) || (rc = poly(0, 1)) ||
-            (rc = sprod(1, a, 1, a, 2)) || (rc = sprod(2, 0.f, 0, 0.f, 3)) || (rc = poly(3, 0)) ||
-            (rc = sprod(0, a, 1, a, 2)) || (rc = applyk(0, 1, 2, 0.f, 0)) ||
-            (rc = gram(1, 0, 0)) || (rc = poly(0, 1)) ||
-            (rc = sprod(1, a, 1, a, 2)) || (rc = sprod(2, 0.f, 0, 0.f, 3)) || (rc = poly(3, 0)) ||
-            (rc = sprod(0, a, 1, a, 2)) ||
-            (rc = sprod(0, a, 0, a, 1)) || (rc = sprod(1, 0.f, 3, 0.f, 0)) || (rc = poly(0, 1)) ||
-            (rc = sprod(1, a, 2, 0.f, 3)) || (rc = applyk(1, 0, 3, 0.f, 1)))
-          return rc;
+    std::vector<NsLaunch> plain = plain_sequence(ch.plain, a), chain = chain_sequence(ch.chain, a);
+    if (ch.plain.mats.empty()) plain.clear();
+    if (ch.chain.mats.empty()) chain.clear();
+    auto list_of = [&](const NsLaunch& l) { return c->d_items + (l.op.kind == GEMM_APPLY ? l.G->off_apply : l.G->off_upper); };
+    auto count_of = [&](const NsLaunch& l) { return l.op.kind == GEMM_APPLY ? l.G->n_apply : l.G->n_upper; };
+    // one product, or two of independent groups (l1) in one small-tile launch
+    auto run = [&](const NsLaunch& l, const NsLaunch* l1) {
+      const NsGroup& G = *l.G;
+      const int h = hilo && l.op.kind != GEMM_POLY ? (l.op.kind == GEMM_GRAM ? 3 : 2) : 1;
+      double bytes = 0, flops = 0, exec = 0;
+      int cls = K_NS_GRAM;
+      switch (l.op.kind) {
+        case GEMM_GRAM: flops = G.alg_rc; exec = G.exec_gram * h; break;
+        case GEMM_POLY: cls = K_NS_POLY; flops = G.alg_rr; exec = G.exec_rr; break;
+        case GEMM_SPROD: cls = K_NS_SPROD; flops = G.alg_rr; exec = G.exec_rr; break;
+        default:
+          cls = K_NS_APPLY;
+          flops = G.alg_rc;
+          exec = G.exec_apply * h;
+          bytes = l.op.last ? G.elems * (2 * wb + db) : 0;
       }
+      return timed(c, cls, bytes, flops, [&] {
+        if (P.tile != kNsTile) {
+          NsStepParams sp;
+          sp.a = p.a; sp.b = p.b; sp.c = p.c; sp.lr = p.lr; sp.decay = p.decay; sp.dscale = p.dscale;
+          sp.write_d = p.write_d; sp.hilo = p.hilo; sp.wtype = wt;
+          return launch_ns_small(P.tile, md, list_of(l), count_of(l), l.op, l1 ? list_of(*l1) : nullptr,
+                                 l1 ? count_of(*l1) : 0, l1 ? l1->op : l.op, sp, c->stream);
+        }
+        p.src = l.op.src; p.use_alpha = l.op.use_alpha; p.last = l.op.last;
+        p.sx = l.op.sx; p.sy = l.op.sy; p.so = l.op.so; p.xshift = l.op.xshift; p.yshift = l.op.yshift;
+        return launch_ns_gemm((GemmKind)l.op.kind, wt, md, list_of(l), count_of(l), p, c->stream, hilo);
+      }, exec);
+    };
+    // the two groups are independent: on small tiles, the k-th products of both
+    // share a launch (each has its own when profiling)
+    for (size_t k = 0; k < std::max(plain.size(), chain.size()); ++k) {
+      const NsLaunch* x = k < chain.size() ? &chain[k] : nullptr;
+      const NsLaunch* y = k < plain.size() ? &plain[k] : nullptr;
+      if (x && y && !c->prof && P.tile != kNsTile) {
+        if ((rc = run(*x, y))) return rc;
+        continue;
+      }
+      if (x && (rc = run(*x, nullptr))) return rc;
+      if (y && (rc = run(*y, nullptr))) return rc;
     }
   }
   return PRM_OK;
@@ -1272,15 +1406,29 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   const int rho = refresh_of(c2, step);
   // scratch layout: descriptor | int lists | work lists | per-matrix scalars |
   // NS5 workspace (refresh) or tall column statistics (row-wise)
-  const int64_t T = P.rp[0] / kNsTile, tc = P.cp[0] / kNsTile;
-  const int64_t pn = (P.tall[0] ? P.rp[0] : P.cp[0]) / kPrologueTile;
-  const int64_t pm = (P.tall[0] ? P.cp[0] : P.rp[0]) / kPrologueTile;
-  const int64_t slabs = (P.nn[0] + 255) / 256;
-  const int64_t nitems = rho ? pm * pn + T * (T + 1) / 2 + tc * T : (P.tall[0] ? (int64_t)P.nrb[0] * slabs + slabs : 0);
-  const uint64_t off_ints = align256(sizeof(MatDesc)), off_items = off_ints + 256;
-  const uint64_t off_small = off_items + align256((uint64_t)std::max<int64_t>(nitems, 1) * sizeof(Item));
-  const uint64_t off_big = off_small + align256(P.small_bytes);
-  const uint64_t need = off_big + (rho ? P.chunk_bytes : P.tall_bytes);
+  int64_t T, tc, pn, pm, slabs;
+  uint64_t off_ints, off_items, off_small, off_big, need;
+  auto layout = [&]() {
+    T = P.rp[0] / P.tile;
+    tc = P.cp[0] / P.tile;
+    pn = (P.tall[0] ? P.rp[0] : P.cp[0]) / kPrologueTile;
+    pm = (P.tall[0] ? P.cp[0] : P.rp[0]) / kPrologueTile;
+    slabs = (P.nn[0] + 255) / 256;
+    const int64_t n = rho ? pm * pn + T * (T + 1) / 2 + tc * T : (P.tall[0] ? (int64_t)P.nrb[0] * slabs + slabs : 0);
+    off_ints = align256(sizeof(MatDesc));
+    off_items = off_ints + 256;
+    off_small = off_items + align256((uint64_t)std::max<int64_t>(n, 1) * sizeof(Item));
+    off_big = off_small + align256(P.small_bytes);
+    need = off_big + (rho ? P.chunk_bytes : P.tall_bytes);
+    return n;
+  };
+  int64_t nitems = layout();
+  if (need > PRM_NOALLOC_SCRATCH_BYTES && P.tile != kNsTile) {
+    // smaller tiles have longer work lists; what fits on the largest one is taken
+    rc = make_plan(1, &rows, &cols, &c2, P, kNsTile);
+    if (rc) return rc;
+    nitems = layout();
+  }
   if (need > PRM_NOALLOC_SCRATCH_BYTES)
     return fail(PRM_ENOMEM, "a %s step of a %lld x %lld matrix needs %llu scratch bytes; the allocation-free step has %llu",
                 rho ? "refresh" : "row-wise", (long long)rows, (long long)cols, (unsigned long long)need,
@@ -1293,8 +1441,8 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   NoallocSetup s;
   std::memset(&s, 0, sizeof(s));
   int32_t pos = 0;
-  auto add = [&](size_t& off, size_t count, int64_t want, int64_t dim, int upper) {
-    if ((int64_t)count != want || s.nseg == kNoallocSegs) return false;
+  auto add = [&](size_t& off, int64_t count, int64_t dim, int upper) {
+    if (s.nseg == kNoallocSegs) return false;
     off = (size_t)pos;
     s.seg[s.nseg++] = NoallocSeg{pos, (int32_t)count, (int32_t)dim, upper};
     pos += (int32_t)count;
@@ -1304,14 +1452,15 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   if (rho) {
     Chunk& ch = P.chunks[0];
     NsGroup& G = P.chain[0] ? ch.chain : ch.plain;  // the other group is empty
-    ok = add(ch.off_prologue, ch.prologue.size(), pm * pn, pn, 0) &&
-         add(G.off_upper, G.upper.size(), T * (T + 1) / 2, T, 1) &&
-         add(G.off_apply, G.apply.size(), tc * T, T, 0);
+    G.n_upper = (int32_t)(T * (T + 1) / 2);
+    G.n_apply = (int32_t)(tc * T);
+    ok = (int64_t)ch.prologue.size() == pm * pn && add(ch.off_prologue, pm * pn, pn, 0) &&
+         add(G.off_upper, G.n_upper, T, 1) && add(G.off_apply, G.n_apply, T, 0);
   } else if (P.tall[0]) {
     const bool v4 = !P.tall_items4.empty();
-    ok = add(v4 ? P.off_tall4 : P.off_tall1, v4 ? P.tall_items4.size() : P.tall_items1.size(),
-             (int64_t)P.nrb[0] * slabs, slabs, 0) &&
-         add(P.off_fin, P.fin_items.size(), slabs, slabs, 0);
+    ok = (int64_t)(v4 ? P.tall_items4 : P.tall_items1).size() == (int64_t)P.nrb[0] * slabs &&
+         (int64_t)P.fin_items.size() == slabs &&
+         add(v4 ? P.off_tall4 : P.off_tall1, (int64_t)P.nrb[0] * slabs, slabs, 0) && add(P.off_fin, slabs, slabs, 0);
   }
   if (!ok || pos != nitems) return fail(PRM_EHIP, "internal: work list sizes disagree with the plan");
   s.nints = (int32_t)P.ints.size();

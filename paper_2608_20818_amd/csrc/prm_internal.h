@@ -21,7 +21,7 @@ struct MatDesc {
   float s;       // shape scale s(W)
   int32_t tall;  // m > n: oriented rows are stored columns
   // NS5 workspace (bf16 bit patterns), valid while this matrix's chunk runs.
-  // Oriented r x c is padded to rp x cp (multiples of the GEMM tile); the
+  // Oriented r x c is padded to rp x cp (multiples of the plan's GEMM tile); the
   // iterate is kept transposed, XT = X^T (cp x rp, row-major).
   uint16_t* XT;   // cp x rp   iterate
   uint16_t* XTn;  // cp x rp   next iterate
@@ -117,6 +117,23 @@ enum GemmKind : int32_t { GEMM_GRAM = 0, GEMM_POLY = 1, GEMM_APPLY = 2, GEMM_SPR
 hipError_t launch_ns_gemm(GemmKind kind, DType wt, const MatDesc* md, const Item* items,
                           int32_t nitems, const NsParams& p, hipStream_t s, bool hilo = false);
 
+// ---- small-tile NS5 products (ns5_small.hip) --------------------------------
+// One product of the NS5 sequence (see NsParams for the fields; a shift is 0
+// or the coefficient a).
+struct NsOp {
+  int32_t kind;       // GemmKind
+  int32_t src, use_alpha, last;
+  int32_t sx, sy, so;
+  float xshift, yshift;
+};
+struct NsStepParams {
+  float a, b, c, lr, decay, dscale;
+  int32_t write_d, hilo, wtype;
+};
+// op0 over the n0 tiles of items0 and op1 over the n1 tiles of items1
+hipError_t launch_ns_small(int tile, const MatDesc* md, const Item* items0, int32_t n0, const NsOp& op0,
+                           const Item* items1, int32_t n1, const NsOp& op1, const NsStepParams& p, hipStream_t s);
+
 // calibration probes (probe.hip)
 hipError_t launch_probe_mfma(int blocks, float* sink, unsigned long long* clk, int iters, hipStream_t s);
 // kind 0: read x, 1: write y, 2: copy x -> y; n16 16-byte elements; kind 3:
@@ -154,7 +171,8 @@ constexpr int kAdamwChunk = 2048;  // elements per block: 256 threads x 2 pieces
 hipError_t launch_adamw(DType pt, DType gt, const AuxDesc* desc, const AuxChunk* chunks, int32_t nchunks,
                         const AdamwParams& p, hipStream_t s);
 
-// GEMM tile edge used by the NS5 kernels; rp and cp are multiples of it.
+// Tile edge of the large NS5 GEMMs (ns5.hip); rp and cp are multiples of the
+// plan's tile edge: this one, or 64 or 128 (ns5_small.hip).
 constexpr int kNsTile = 256;
 // Prologue tile edge.
 constexpr int kPrologueTile = 64;

@@ -1,0 +1,93 @@
+"""The NS5 products on 64 x 64 and 128 x 128 tiles (small weight sets) against
+the oracle: one tile, one past a tile, several tiles, a ragged last one; every
+product kind (plain, factored and precise sequences), both groups in one launch,
+both parameter types and rows that are no multiple of 8 long."""
+import os
+import re
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import paper_2608_20818_amd as prm  # noqa: E402
+import prm_case as pc  # noqa: E402
+from oracle import prm_oracle as po  # noqa: E402
+
+SETS = {
+    # r on both sides of a tile, plain (c < 2r) and factored, wide and tall
+    64: [[(64, 64)], [(1, 200), (200, 1)], [(63, 127), (65, 64), (129, 65)], [(64, 128), (130, 260), (100, 101), (261, 127)]],
+    128: [[(1400, 3003), (1400, 1401)],
+          [(1100, 1120), (1101, 3003), (1000, 1001), (2400, 1101), (1155, 577), (50, 2310)]],
+}
+
+
+def exec_rr(shapes, tile):
+    """FLOPs one launch of the square runs over the set: upper tiles, whole."""
+    total = 0
+    for m, n in shapes:
+        t = -(-min(m, n) // tile)
+        total += t * (t + 1) // 2 * 2 * tile ** 3 * t
+    return total
+
+
+CASES = [(t, i, p) for t in SETS for i in range(len(SETS[t])) for p in (0, 1)]
+
+
+@pytest.mark.parametrize("wdt,gdt", [(1, 1), (0, 0)])
+@pytest.mark.parametrize("tile,i,precise", CASES)
+@pytest.mark.gpu
+@pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")
+def test_small_tiles_against_the_oracle(tile, i, precise, wdt, gdt):
+    shapes = SETS[tile][i]
+    cfg = prm.config_default(K=2, lr=0.02, wd=0.1, param_dtype=wdt, grad_dtype=gdt, ns_precise=precise)
+    oc = pc.oracle_config(cfg)
+    inputs = pc.host_inputs(shapes, cfg, 88, steps=(0,))
+    W = [pc.to_device(w, wdt) for w, _, _ in inputs]
+    M = [pc.to_device(m, 0) for _, m, _ in inputs]
+    G = [pc.to_device(g[0], gdt) for _, _, g in inputs]
+    D = [torch.zeros(s, dtype=torch.float32, device="cuda") for s in shapes]
+    Wt, Mt = [w.clone() for w in W], [m.clone() for m in M]
+    Wt2, Mt2 = [w.clone() for w in W], [m.clone() for m in M]
+    print(f"  tile {tile} {shapes} precise={precise}", flush=True)
+    with prm.Optimizer(shapes, cfg) as opt:
+        assert opt.step(W, G, M, 0, directions=D) == 1
+        assert opt.step(Wt, G, Mt, 0) == 1  # without directions: the same bits
+        torch.cuda.synchronize()
+        # the executed FLOPs of the squares show the tile the planner chose
+        opt.profile_enable(True)
+        opt.step(Wt2, G, Mt2, 0)
+        stats = opt.profile_read()["ns_poly"]
+        assert stats["exec_flops"] == 5 * exec_rr(shapes, tile)  # five squares in either form
+    for k, (w0, m0, g) in enumerate(inputs):
+        Wo, Mo, Do, _ = po.step_matrix(w0, m0, g[0], 0, oc)
+        eD = pc.rel(pc.to_host(D[k]), Do)
+        print(f"  {shapes[k]} D err {eD:.2e}", flush=True)
+        assert eD <= pc.TOL_NS5
+        assert pc.rel(pc.to_host(M[k]), Mo) <= pc.TOL_M
+        # W = decay W0 - lr D with the GPU's own D, rounded once to its type
+        if wdt == prm.BF16:
+            assert pc.bf16_write_bound(pc.to_host(W[k]), Wo, pc.to_host(D[k]), Do, cfg.lr) <= 1.0
+        else:
+            lr = pc.f32(cfg.lr)
+            diff = np.abs((pc.to_host(W[k]) - Wo) + lr * (pc.to_host(D[k]) - Do))
+            assert diff.max() <= 2.0 ** -22 * (np.abs(Wo).max() + lr * np.abs(Do).max())
+        assert torch.equal(W[k], Wt[k]) and torch.equal(M[k], Mt[k])
+
+
+def test_small_gemm_assembly_keeps_m0_and_its_wait_state(tmp_path):
+    """The stage loads' inline assembly writes M0, which the compiler reserves
+    and does not save: no compiler-made M0 reader may be in the file, and every
+    load into LDS needs an instruction between the M0 write and itself."""
+    from paper_2608_20818_amd import build as b
+    from test_abi import _m0_check
+    out = tmp_path / "ns5_small.s"
+    r = subprocess.run([b.hipcc(), *b.FLAGS, *b.EXTRA["ns5_small.hip"], "--cuda-device-only", "-S",
+                        os.path.join(b.CSRC, "ns5_small.hip"), "-o", str(out)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    text = out.read_text()
+    readers, asm_dma, bad = _m0_check(text)
+    assert asm_dma > 0 and readers == 0 and not bad
+    assert not re.search(r"s_mov_b32 m0, \S+\n\s*global_load_lds", text)
