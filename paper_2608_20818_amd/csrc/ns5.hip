@@ -332,7 +332,8 @@ __global__ __launch_bounds__(gemm::NTHREADS, 1) void ns_gemm_kernel(const MatDes
   // destination of the DMA) is a register the compiler reserves and does not
   // save around the asm; in these kernels its own code reads M0 only for the
   // square epilogue's LDS DMA and writes it right before each such read (the
-  // compiled assembly is checked for this by tests/test_abi.py).
+  // compiled assembly is checked for this by tests/test_abi.py).  The s_nop
+  // is the wait state that a load into LDS needs after an M0 write.
   // `sg`: the K segment (0 unless NSEG > 1), `k` the offset within it
   auto dma1 = [&](char* stage, int sg, int64_t k, int q) __attribute__((always_inline)) {
     const bool isb = q >= DMA_PER_WAVE;
@@ -352,7 +353,7 @@ __global__ __launch_bounds__(gemm::NTHREADS, 1) void ns_gemm_kernel(const MatDes
     const uint32_t lds = (uint32_t)(uintptr_t)(lds_ptr)(stage + (isb ? A_BYTES : 0) + (DMA_PER_WAVE * wave + qq) * 1024);
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"  // the M0 clobber, see above
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff[qq]), "s"(base), "s"(lds) : "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff[qq]), "s"(base), "s"(lds) : "m0");
 #pragma clang diagnostic pop
   };
   auto stage_landed = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
