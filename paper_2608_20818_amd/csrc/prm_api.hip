@@ -96,6 +96,7 @@ const char* kClassName[K_NCLASS] = {"rw_wide", "rw_generic", "rw_tall_stats",
 
 struct WideClass {
   int tpr, nch;
+  bool aligned;  // row lengths are multiples of 8
   std::vector<int32_t> mats, starts;
   int32_t nblocks = 0;
   size_t off_mats = 0, off_starts = 0;
@@ -118,6 +119,7 @@ struct NsGroup {
 struct Chunk {
   std::vector<int32_t> mats;
   std::vector<Item> prologue;
+  int32_t n_prologue = 0;
   size_t off_mats = 0, off_prologue = 0;
   double elems = 0;
   NsGroup plain, chain;  // five iterations as written; the factored form
@@ -138,9 +140,17 @@ struct Plan {
   uint64_t chunk_bytes = 0, small_bytes = 0, tall_bytes = 0, total_bytes = 0;
   std::vector<WideClass> wide;
   WideClass generic;
+  // tall matrices: tiles of both passes (widths that are multiples of 4 and
+  // the others) and column slabs of the finalize
   std::vector<Item> tall_items4, tall_items1, fin_items;
+  int32_t n_tall4 = 0, n_tall1 = 0, n_fin = 0;
   size_t off_tall4 = 0, off_tall1 = 0, off_fin = 0;
   double tall_elems4 = 0, tall_elems1 = 0;
+  int own_norms = 0;     // the second pass sums the statistics itself (no finalize)
+  // one launch for every first pass: the tall statistics and the wide matrices
+  // whose rows a block of 256 threads holds (their segments)
+  int rw_first = 0;
+  WideClass first;
   std::vector<Chunk> chunks;
   std::vector<int32_t> ints;   // all int32 lists, uploaded once
   std::vector<Item> items;     // all item lists, uploaded once
@@ -201,16 +211,22 @@ uint64_t ns_matrix_bytes(int64_t rp, int64_t cp, int chain, int precise) {
   return (uint64_t)ns_iterates(precise) * g.iterate + (uint64_t)ns_splits(chain) * (g.split + g.diag);
 }
 
-// Row-wise launch class of a wide row of length n (0 tpr = generic path).
+// Row-wise launch class of a wide row of length n: threads per row and chunks of
+// 8 per thread (0 tpr: the two-sweep path).  Ragged rows take a block each from
+// kRaggedWaveRow on (their sums do not depend on it, and four waves a row keep a
+// set of few rows in flight) and the two-sweep path where a block's registers end.
 void wide_class(int64_t n, int& tpr, int& nch) {
+  const int64_t chunks = std::max<int64_t>(1, n / 8);
   tpr = 0;
   nch = 0;
-  if (n % 8 != 0) return;
-  const int64_t chunks = n / 8;
-  if (chunks <= 64 * 8) { tpr = 64; nch = (int)((chunks + 63) / 64); }
+  if (n <= (n % 8 ? kRaggedWaveRow : kWaveRow)) { tpr = 64; nch = (int)((chunks + 63) / 64); }
   else if (chunks <= 256 * 8) { tpr = 256; nch = (int)((chunks + 255) / 256); }
-  else if (chunks <= 512 * 8) { tpr = 512; nch = (int)((chunks + 511) / 512); }
+  else if (chunks <= 512 * 8 && n % 8 == 0) { tpr = 512; nch = (int)((chunks + 511) / 512); }
 }
+
+// Tall matrices up to this many row blocks: every tile of the second pass sums
+// its columns' partials itself.
+constexpr int kOwnNormBlocks = 64;
 
 // Tile edge of the plan's NS5 products: 256 runs its MFMAs best, smaller tiles
 // spread a small set over more CUs and pad less.  Each product is priced as if
@@ -402,49 +418,73 @@ struct XcdLists {
   }
 };
 
-// Work lists (host side); built only by prm_init.
-void build_lists(Plan& P, const prm_config* cfg) {
+// Work lists (host side).  `items` false (the allocation-free step, which writes
+// its one matrix's lists on the device): only their lengths.
+void build_lists(Plan& P, bool items) {
   // row-wise wide classes
+  int most_blocks = 0, firsts = 0;
   for (int i = 0; i < P.n; ++i) {
+    most_blocks = std::max(most_blocks, P.nrb[i]);
     if (P.tall[i]) continue;
+    const int64_t n = P.nn[i];
     int tpr, nch;
-    wide_class(P.nn[i], tpr, nch);
+    wide_class(n, tpr, nch);
     WideClass* wc = nullptr;
     if (tpr == 0) {
       wc = &P.generic;
     } else {
+      const bool al = n % 8 == 0;
       for (auto& w : P.wide)
-        if (w.tpr == tpr && w.nch == nch) wc = &w;
+        if (w.tpr == tpr && w.nch == nch && w.aligned == al) wc = &w;
       if (!wc) {
         P.wide.emplace_back();
         wc = &P.wide.back();
         wc->tpr = tpr;
         wc->nch = nch;
+        wc->aligned = al;
       }
     }
-    const int rpb = (tpr == 64) ? 4 : 1;
-    wc->mats.push_back(i);
-    wc->starts.push_back(wc->nblocks);
-    wc->nblocks += (int32_t)((P.m[i] + rpb - 1) / rpb);
-    wc->elems += (double)P.m[i] * P.nn[i];
+    auto put = [&](WideClass& w, int rows_per_block) {
+      w.mats.push_back(i);
+      w.starts.push_back(w.nblocks);
+      w.nblocks += (int32_t)((P.m[i] + rows_per_block - 1) / rows_per_block);
+      w.elems += (double)P.m[i] * n;
+    };
+    put(*wc, tpr == 64 ? 4 : 1);
+    if (tpr == 64 || tpr == 256) put(P.first, tpr == 64 ? 4 : 1);
   }
+  P.own_norms = most_blocks <= kOwnNormBlocks;
   // tall lists
   for (int i = 0; i < P.n; ++i) {
     if (!P.tall[i]) continue;
-    const int vec = (P.nn[i] % 4 == 0) ? 4 : 1;
     const int64_t slabs = (P.nn[i] + 255) / 256;  // 256-column tiles
-    auto& L = vec == 4 ? P.tall_items4 : P.tall_items1;
+    const int32_t fins = (int32_t)((P.nn[i] + kFinCols - 1) / kFinCols);
+    const bool al = P.nn[i] % 4 == 0;
+    (al ? P.n_tall4 : P.n_tall1) += (int32_t)(P.nrb[i] * slabs);
+    (al ? P.tall_elems4 : P.tall_elems1) += (double)P.m[i] * P.nn[i];
+    P.n_fin += fins;
+    if (!items) continue;
+    auto& L = al ? P.tall_items4 : P.tall_items1;
     for (int32_t rb = 0; rb < P.nrb[i]; ++rb)
       for (int32_t sb = 0; sb < slabs; ++sb) L.push_back(Item{i, rb, sb, 0});
-    (vec == 4 ? P.tall_elems4 : P.tall_elems1) += (double)P.m[i] * P.nn[i];
-    for (int32_t cb = 0; cb < (P.nn[i] + 255) / 256; ++cb) P.fin_items.push_back(Item{i, 0, cb, 0});
+    for (int32_t cb = 0; cb < fins; ++cb) P.fin_items.push_back(Item{i, 0, cb, 0});
   }
+  // one launch for all of them instead of one per class and pass, over the weights
+  // of one to three blocks of width 384 to 2560: 28 -> 18 us at 2.2 M elements,
+  // 117 -> 95 at 25 M, 617 -> 598 at 189 M, 1089 -> 1044 at 295 M; but 4000 ->
+  // 4083 at 1.26 G, where the ends of the launches weigh less than the registers
+  // of the longest rows
+  double elems = 0;
+  for (int i = 0; i < P.n; ++i) elems += (double)P.m[i] * P.nn[i];
+  for (const auto& w : P.wide) firsts += w.tpr != 512;
+  P.rw_first = elems <= 4e8 && firsts + (P.n_tall4 > 0) + (P.n_tall1 > 0) > 1;
   // NS5 lists per chunk and group
   for (auto& ch : P.chunks) {
     for (int i : ch.mats) {
       const int64_t pm = (P.tall[i] ? P.cp[i] : P.rp[i]) / kPrologueTile;
       const int64_t pn = (P.tall[i] ? P.rp[i] : P.cp[i]) / kPrologueTile;
-      for (int32_t a = 0; a < pm; ++a)
+      ch.n_prologue += (int32_t)(pm * pn);
+      for (int32_t a = 0; items && a < pm; ++a)
         for (int32_t b = 0; b < pn; ++b) ch.prologue.push_back(Item{i, a, b, 0});
       ch.elems += (double)P.m[i] * P.nn[i];
     }
@@ -471,6 +511,11 @@ void build_lists(Plan& P, const prm_config* cfg) {
         G.exec_rr += upper * 2 * t2 * rp;
         // the large-tile apply's diagonal term adds 64 MFMAs per wave to 64 per stage
         G.exec_apply += (double)tc * tr * 2 * t2 * rp * (P.tile == kNsTile ? 1.0 + kNsTile / 4.0 / rp : 1.0);
+        if (!items) {
+          G.n_upper += tr * (tr + 1) / 2;
+          G.n_apply += tc * tr;
+          continue;
+        }
         tiles.clear();
         tile_order(i, tr, tr, true, tiles);
         u.add(tiles, cp);
@@ -479,13 +524,13 @@ void build_lists(Plan& P, const prm_config* cfg) {
         tile_order(i, tc, tr, false, tiles);
         a.add(tiles, rp);
       }
+      if (!items) continue;
       G.upper = u.interleaved();
       G.apply = a.interleaved();
       G.n_upper = (int32_t)G.upper.size();
       G.n_apply = (int32_t)G.apply.size();
     }
   }
-  (void)cfg;
   // flatten
   auto put_ints = [&](const std::vector<int32_t>& v) {
     size_t o = P.ints.size();
@@ -501,10 +546,14 @@ void build_lists(Plan& P, const prm_config* cfg) {
     w.off_mats = put_ints(w.mats);
     w.off_starts = put_ints(w.starts);
   }
+  if (P.rw_first) {
+    P.first.off_mats = put_ints(P.first.mats);
+    P.first.off_starts = put_ints(P.first.starts);
+  }
   P.generic.off_mats = put_ints(P.generic.mats);
   P.generic.off_starts = put_ints(P.generic.starts);
   P.off_tall4 = put_items(P.tall_items4);
-  P.off_tall1 = put_items(P.tall_items1);
+  P.off_tall1 = put_items(P.tall_items1);  // right behind: the one launch takes both
   P.off_fin = put_items(P.fin_items);
   for (auto& ch : P.chunks) {
     ch.off_mats = put_ints(ch.mats);
@@ -663,36 +712,42 @@ int rowwise_step(prm_ctx* c, float lr, bool debug) {
   const double gb = gt == BF16 ? 2 : 4, wb = wt == BF16 ? 2 : 4, db = debug ? 4 : 0;
   const MatDesc* md = c->d_desc;
   int rc;
-  // tall matrices first (column statistics, then their parameter write)
-  for (int v : {4, 1}) {
-    const auto& L = v == 4 ? P.tall_items4 : P.tall_items1;
-    if (L.empty()) continue;
-    const Item* items = c->d_items + (v == 4 ? P.off_tall4 : P.off_tall1);
-    const double el = v == 4 ? P.tall_elems4 : P.tall_elems1;
-    rc = timed(c, K_RW_TALL_STATS, el * (gb + 8), 0, [&] {
-      return launch_rw_tall_stats(v, gt, md, items, (int32_t)L.size(), p, c->stream);
+  const int32_t n4 = P.n_tall4, n1 = P.n_tall1;
+  const Item *t4 = c->d_items + P.off_tall4, *t1 = c->d_items + P.off_tall1;
+  // every first pass in one launch (each on its own when profiling; the results
+  // are the same bits); tall matrices: column statistics, then their parameter write
+  const bool first = P.rw_first && !c->prof;
+  if (first) {
+    rc = timed(c, K_RW_WIDE, 0, 0, [&] {
+      return launch_rw_first(wt, gt, md, t4, n4 + n1, c->d_ints + P.first.off_mats, c->d_ints + P.first.off_starts,
+                             (int32_t)P.first.mats.size(), P.first.nblocks, p, c->stream);
     });
     if (rc) return rc;
   }
-  if (!P.fin_items.empty()) {
+  for (int al : {1, 0}) {
+    if (first || !(al ? n4 : n1)) continue;
+    rc = timed(c, K_RW_TALL_STATS, (al ? P.tall_elems4 : P.tall_elems1) * (gb + 8), 0, [&] {
+      return launch_rw_tall_stats(al, gt, md, al ? t4 : t1, al ? n4 : n1, p, c->stream);
+    });
+    if (rc) return rc;
+  }
+  if (P.n_fin && !P.own_norms) {
     rc = timed(c, K_RW_TALL_FIN, 0, 0, [&] {
-      return launch_rw_tall_finalize(md, c->d_items + P.off_fin, (int32_t)P.fin_items.size(), p, c->stream);
+      return launch_rw_tall_finalize(md, c->d_items + P.off_fin, P.n_fin, p, c->stream);
     });
     if (rc) return rc;
   }
-  for (int v : {4, 1}) {
-    const auto& L = v == 4 ? P.tall_items4 : P.tall_items1;
-    if (L.empty()) continue;
-    const Item* items = c->d_items + (v == 4 ? P.off_tall4 : P.off_tall1);
-    const double el = v == 4 ? P.tall_elems4 : P.tall_elems1;
-    rc = timed(c, K_RW_TALL_APPLY, el * (2 * wb + db), 0, [&] {
-      return launch_rw_tall_apply(v, wt, gt, md, items, (int32_t)L.size(), p, c->stream);
+  for (int al : {1, 0}) {
+    if (!(al ? n4 : n1)) continue;
+    rc = timed(c, K_RW_TALL_APPLY, (al ? P.tall_elems4 : P.tall_elems1) * (2 * wb + db), 0, [&] {
+      return launch_rw_tall_apply(al, P.own_norms, wt, gt, md, al ? t4 : t1, al ? n4 : n1, p, c->stream);
     });
     if (rc) return rc;
   }
   for (const auto& w : P.wide) {
+    if (first && w.tpr != 512) continue;
     rc = timed(c, K_RW_WIDE, w.elems * (gb + 8 + 2 * wb + db), 0, [&] {
-      return launch_rw_wide(w.tpr, w.nch, wt, gt, md, c->d_ints + w.off_mats,
+      return launch_rw_wide(w.tpr, w.nch, w.aligned, wt, gt, md, c->d_ints + w.off_mats,
                             c->d_ints + w.off_starts, (int32_t)w.mats.size(), w.nblocks, p,
                             c->stream);
     });
@@ -785,7 +840,7 @@ int refresh_step(prm_ctx* c, float lr, bool debug) {
   int rc;
   for (const auto& ch : P.chunks) {
     rc = timed(c, K_NS_PROLOGUE, ch.elems * (gb + 8 + (hilo ? 4 : 2)), 0, [&] {  // G, M read; M, bf16 X^T (hi, lo) written
-      return launch_ns_prologue(gt, md, c->d_items + ch.off_prologue, (int32_t)ch.prologue.size(), p, c->stream);
+      return launch_ns_prologue(gt, md, c->d_items + ch.off_prologue, ch.n_prologue, p, c->stream);
     });
     if (rc) return rc;
     rc = timed(c, K_NS_ALPHA, 0, 0, [&] {
@@ -1056,7 +1111,7 @@ int prm_init(prm_ctx** out, int32_t n_mats, const int64_t* rows, const int64_t* 
   }
   c->cfg = *cfg;
   c->stream = (hipStream_t)hip_stream;
-  build_lists(c->plan, cfg);
+  build_lists(c->plan, true);
   Plan& P = c->plan;
   auto cleanup = [&](int code) {
     prm_destroy(c);
@@ -1406,7 +1461,7 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   const int rho = refresh_of(c2, step);
   // scratch layout: descriptor | int lists | work lists | per-matrix scalars |
   // NS5 workspace (refresh) or tall column statistics (row-wise)
-  int64_t T, tc, pn, pm, slabs;
+  int64_t T, tc, pn, pm, slabs, fins;
   uint64_t off_ints, off_items, off_small, off_big, need;
   auto layout = [&]() {
     T = P.rp[0] / P.tile;
@@ -1414,7 +1469,8 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
     pn = (P.tall[0] ? P.rp[0] : P.cp[0]) / kPrologueTile;
     pm = (P.tall[0] ? P.cp[0] : P.rp[0]) / kPrologueTile;
     slabs = (P.nn[0] + 255) / 256;
-    const int64_t n = rho ? pm * pn + T * (T + 1) / 2 + tc * T : (P.tall[0] ? (int64_t)P.nrb[0] * slabs + slabs : 0);
+    fins = (P.nn[0] + kFinCols - 1) / kFinCols;
+    const int64_t n = rho ? pm * pn + T * (T + 1) / 2 + tc * T : (P.tall[0] ? (int64_t)P.nrb[0] * slabs + fins : 0);
     off_ints = align256(sizeof(MatDesc));
     off_items = off_ints + 256;
     off_small = off_items + align256((uint64_t)std::max<int64_t>(n, 1) * sizeof(Item));
@@ -1433,7 +1489,7 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
     return fail(PRM_ENOMEM, "a %s step of a %lld x %lld matrix needs %llu scratch bytes; the allocation-free step has %llu",
                 rho ? "refresh" : "row-wise", (long long)rows, (long long)cols, (unsigned long long)need,
                 (unsigned long long)PRM_NOALLOC_SCRATCH_BYTES);
-  build_lists(P, &c2);
+  build_lists(P, false);
   if (P.ints.size() > 64) return fail(PRM_EHIP, "internal: %zu int list entries", P.ints.size());
   for (int32_t v : P.ints)
     if (v != 0) return fail(PRM_EHIP, "internal: nonzero int list entry for one matrix");
@@ -1452,15 +1508,13 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   if (rho) {
     Chunk& ch = P.chunks[0];
     NsGroup& G = P.chain[0] ? ch.chain : ch.plain;  // the other group is empty
-    G.n_upper = (int32_t)(T * (T + 1) / 2);
-    G.n_apply = (int32_t)(tc * T);
-    ok = (int64_t)ch.prologue.size() == pm * pn && add(ch.off_prologue, pm * pn, pn, 0) &&
-         add(G.off_upper, G.n_upper, T, 1) && add(G.off_apply, G.n_apply, T, 0);
+    ok = ch.n_prologue == pm * pn && G.n_upper == T * (T + 1) / 2 && G.n_apply == tc * T &&
+         add(ch.off_prologue, ch.n_prologue, pn, 0) && add(G.off_upper, G.n_upper, T, 1) &&
+         add(G.off_apply, G.n_apply, T, 0);
   } else if (P.tall[0]) {
-    const bool v4 = !P.tall_items4.empty();
-    ok = (int64_t)(v4 ? P.tall_items4 : P.tall_items1).size() == (int64_t)P.nrb[0] * slabs &&
-         (int64_t)P.fin_items.size() == slabs &&
-         add(v4 ? P.off_tall4 : P.off_tall1, (int64_t)P.nrb[0] * slabs, slabs, 0) && add(P.off_fin, slabs, slabs, 0);
+    const int32_t nt = P.n_tall4 + P.n_tall1;
+    ok = nt == P.nrb[0] * slabs && P.n_fin == fins && add(P.n_tall4 ? P.off_tall4 : P.off_tall1, nt, slabs, 0) &&
+         add(P.off_fin, fins, fins, 0);
   }
   if (!ok || pos != nitems) return fail(PRM_EHIP, "internal: work list sizes disagree with the plan");
   s.nints = (int32_t)P.ints.size();

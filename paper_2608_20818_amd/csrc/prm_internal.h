@@ -89,19 +89,28 @@ enum DType : int32_t { F32 = 0, BF16 = 1 };
 // ---- launchers (defined in rowwise.hip / ns5.hip) -------------------------
 // Wide/square matrices, whole rows held in registers.  seg_start[i] is the
 // first block of segment i (matrix seg_mat[i]); nblocks blocks in total.
-hipError_t launch_rw_wide(int tpr, int nch, DType wt, DType gt, const MatDesc* md,
+// aligned: every row length of the launch is a multiple of 8.
+hipError_t launch_rw_wide(int tpr, int nch, bool aligned, DType wt, DType gt, const MatDesc* md,
                           const int32_t* seg_mat, const int32_t* seg_start, int32_t nseg,
                           int32_t nblocks, const RwParams& p, hipStream_t s);
-// Any shape (unaligned rows, very long rows): two sweeps over the row.
+// Rows too long for registers: two sweeps over the row.
 hipError_t launch_rw_generic(DType wt, DType gt, const MatDesc* md, const int32_t* rows_mat,
                              const int32_t* rows_start, int32_t nseg, int32_t nrows_total,
                              const RwParams& p, hipStream_t s);
-// Tall matrices: column statistics, column norms, parameter write.
-hipError_t launch_rw_tall_stats(int vec, DType gt, const MatDesc* md, const Item* items,
+// First passes in one launch: tall statistics (ntall items) and wide rows (segments of blocks:
+// four rows of at most kWaveRow (ragged: kRaggedWaveRow) elements or one of at
+// most four times kWaveRow) in one launch.
+hipError_t launch_rw_first(DType wt, DType gt, const MatDesc* md, const Item* items, int32_t ntall,
+                           const int32_t* seg_mat, const int32_t* seg_start, int32_t nseg, int32_t nblocks,
+                           const RwParams& p, hipStream_t s);
+// Tall matrices: column statistics, column norms, parameter write (own_norms:
+// the last sums the statistics itself).  aligned: every width of the launch is
+// a multiple of 4.
+hipError_t launch_rw_tall_stats(bool aligned, DType gt, const MatDesc* md, const Item* items,
                                 int32_t nitems, const RwParams& p, hipStream_t s);
 hipError_t launch_rw_tall_finalize(const MatDesc* md, const Item* items, int32_t nitems,
                                    const RwParams& p, hipStream_t s);
-hipError_t launch_rw_tall_apply(int vec, DType wt, DType gt, const MatDesc* md,
+hipError_t launch_rw_tall_apply(bool aligned, bool own_norms, DType wt, DType gt, const MatDesc* md,
                                 const Item* items, int32_t nitems, const RwParams& p,
                                 hipStream_t s);
 
@@ -178,5 +187,10 @@ constexpr int kNsTile = 256;
 constexpr int kPrologueTile = 64;
 // Row block of the tall passes (rows of one 256-column tile; 8 per wave).
 constexpr int kTallRows = 32;
+// Longest row that one wave holds in registers (8 chunks of 8 elements per lane),
+// and longest ragged one (n % 8 != 0) that a wave rather than a block takes.
+constexpr int kWaveRow = 4096, kRaggedWaveRow = 511;
+// Columns per block of the tall finalize.
+constexpr int kFinCols = 32;
 
 }  // namespace prm
