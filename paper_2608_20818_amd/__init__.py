@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
 
 __all__ = [
     "PRMError", "Config", "KernelStats", "Optimizer", "AdamWConfig", "AuxAdamW", "load",
@@ -211,6 +212,30 @@ def step_noalloc(cfg: Config, param, grad, momentum, step: int, lr: float = -1.0
 _DT = {F32: "float32", BF16: "bfloat16"}
 
 
+class _Tensors:
+    """What a list of tensors has to be (``dims``: a shape or an element count
+    each; ``dtype`` F32 or BF16), checked natively where ``_marshal.so`` is built."""
+
+    def __init__(self, dims, dtype: int, shapes: bool):
+        self._array = ctypes.c_void_p * max(len(dims), 1)
+        self._pointers = self._spec = None
+        if "torch" in sys.modules:  # without torch there are only raw pointers
+            try:
+                from . import _marshal
+            except ImportError:
+                return
+            self._pointers = _marshal.pointers
+            self._spec = _marshal.spec(list(dims), dtype, shapes)
+
+    def pointers(self, xs):
+        """The array of data pointers, or None: not all of them are plain device
+        tensors as specified (the caller's checks decide then)."""
+        if self._pointers is None:
+            return None
+        a = self._array()
+        return a if self._pointers(self._spec, xs, ctypes.addressof(a)) else None
+
+
 class Optimizer:
     """One libprm context: a fixed list of matrix shapes and a configuration.
 
@@ -228,6 +253,15 @@ class Optimizer:
         ctx = ctypes.c_void_p()
         _check(load().prm_init(ctypes.byref(ctx), n, rows, cols, ctypes.byref(self.cfg), h))
         self._ctx = ctx
+        self._want = {dt: _Tensors(self.shapes, dt, True) for dt in {F32, self.cfg.param_dtype, self.cfg.grad_dtype}}
+
+    def _pointers(self, xs, dtype, what):
+        a = self._want[dtype].pointers(xs)
+        if a is None:
+            self._check_tensors(xs, _DT[dtype], what)
+            skip = what == "directions"  # a matrix whose direction is not wanted
+            a = (ctypes.c_void_p * max(len(self.shapes), 1))(*[0 if skip and x is None else _ptr(x) for x in xs])
+        return a
 
     def _check_tensors(self, xs, dtype_name, what):
         if len(xs) != len(self.shapes):
@@ -244,21 +278,15 @@ class Optimizer:
     def step(self, params, grads, momenta, step: int, lr: float = -1.0, directions=None) -> int:
         """Enqueue optimizer step ``step``; returns rho_t (1 = NS5 refresh).
         ``directions`` (debug): fp32 tensors receiving D, None to skip a matrix."""
-        self._check_tensors(params, _DT[self.cfg.param_dtype], "params")
-        self._check_tensors(grads, _DT[self.cfg.grad_dtype], "grads")
-        self._check_tensors(momenta, "float32", "momenta")
-        n = len(self.shapes)
-        arr = ctypes.c_void_p * max(n, 1)
-        P = arr(*[_ptr(x) for x in params])
-        G = arr(*[_ptr(x) for x in grads])
-        M = arr(*[_ptr(x) for x in momenta])
+        P = self._pointers(params, self.cfg.param_dtype, "params")
+        G = self._pointers(grads, self.cfg.grad_dtype, "grads")
+        M = self._pointers(momenta, F32, "momenta")
         rho = ctypes.c_int32(-1)
         L = load()
         if directions is None:
             _check(L.prm_step(self._ctx, P, G, M, int(step), float(lr), ctypes.byref(rho)))
         else:
-            self._check_tensors(directions, "float32", "directions")
-            D = arr(*[0 if x is None else _ptr(x) for x in directions])
+            D = self._pointers(directions, F32, "directions")
             _check(L.prm_step_debug(self._ctx, P, G, M, int(step), float(lr), ctypes.byref(rho), D))
         return rho.value
 
@@ -325,6 +353,18 @@ class AuxAdamW:
         ctx = ctypes.c_void_p()
         _check(load().prm_adamw_init(ctypes.byref(ctx), n, arr, ctypes.byref(self.cfg), h))
         self._ctx = ctx
+        self._want = {dt: _Tensors(self.numels, dt, False) for dt in {F32, self.cfg.param_dtype, self.cfg.grad_dtype}}
+
+    def _pointers(self, xs, dtype, what):
+        a = self._want[dtype].pointers(xs)
+        if a is None:
+            self._check_tensors(xs, _DT[dtype], what)
+            a = (ctypes.c_void_p * max(len(self.numels), 1))(*[0 if x is None else _ptr(x) for x in xs])
+        return a
+
+    def _all_pointers(self, params, grads, exp_avg, exp_avg_sq):
+        return (self._pointers(params, self.cfg.param_dtype, "params"), self._pointers(grads, self.cfg.grad_dtype, "grads"),
+                self._pointers(exp_avg, F32, "exp_avg"), self._pointers(exp_avg_sq, F32, "exp_avg_sq"))
 
     def _check_tensors(self, xs, dtype_name, what):
         if len(xs) != len(self.numels):
@@ -340,31 +380,13 @@ class AuxAdamW:
 
     def step(self, params, grads, exp_avg, exp_avg_sq, t: int, lr: float = -1.0):
         """Enqueue the t-th AdamW update (t >= 1, this one included)."""
-        self._check_tensors(params, _DT[self.cfg.param_dtype], "params")
-        self._check_tensors(grads, _DT[self.cfg.grad_dtype], "grads")
-        self._check_tensors(exp_avg, "float32", "exp_avg")
-        self._check_tensors(exp_avg_sq, "float32", "exp_avg_sq")
-        n = len(self.numels)
-        arr = ctypes.c_void_p * max(n, 1)
-
-        def ptrs(xs):
-            return arr(*[0 if x is None else _ptr(x) for x in xs])
-        _check(load().prm_adamw_step(self._ctx, ptrs(params), ptrs(grads), ptrs(exp_avg),
-                                     ptrs(exp_avg_sq), int(t), float(lr)))
+        _check(load().prm_adamw_step(self._ctx, *self._all_pointers(params, grads, exp_avg, exp_avg_sq), int(t), float(lr)))
 
     def bind(self, params, grads, exp_avg, exp_avg_sq):
         """Validate and keep a fixed set of tensors so that ``step_bound`` costs
         one C call (for loops over persistent tensors)."""
-        self._check_tensors(params, _DT[self.cfg.param_dtype], "params")
-        self._check_tensors(grads, _DT[self.cfg.grad_dtype], "grads")
-        self._check_tensors(exp_avg, "float32", "exp_avg")
-        self._check_tensors(exp_avg_sq, "float32", "exp_avg_sq")
-        arr = ctypes.c_void_p * max(len(self.numels), 1)
-
-        def ptrs(xs):
-            return arr(*[0 if x is None else _ptr(x) for x in xs])
+        self._bound = self._all_pointers(params, grads, exp_avg, exp_avg_sq)
         self._keep = (list(params), list(grads), list(exp_avg), list(exp_avg_sq))
-        self._bound = (ptrs(params), ptrs(grads), ptrs(exp_avg), ptrs(exp_avg_sq))
 
     def step_bound(self, t: int, lr: float = -1.0):
         """``step`` on the tensors given to ``bind``."""

@@ -72,6 +72,32 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+MARSHAL_SRC = os.path.join(CSRC, "marshal.cpp")
+MARSHAL_LIB = os.path.join(HERE, "_marshal.so")
+
+
+def build_marshal() -> str:
+    """The binding's native tensor checks (g++, torch's C++ headers, no device
+    code): csrc/marshal.cpp -> _marshal.so, a CPython module."""
+    import sysconfig
+
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    inc = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           sysconfig.get_paths()["include"]]
+    tmp = MARSHAL_LIB + ".tmp"
+    cmd = [shutil.which("g++") or "g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *[f"-I{i}" for i in inc], MARSHAL_SRC,
+           "-o", tmp, "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        print(r.stdout, r.stderr, file=sys.stderr)
+        raise RuntimeError("g++ failed for csrc/marshal.cpp")
+    os.replace(tmp, MARSHAL_LIB)
+    return MARSHAL_LIB
+
+
 C_CALLER_SRC = os.path.join(ROOT, "tests", "c_caller.c")
 C_CALLER_LIB = os.path.join(ROOT, "tests", "libc_caller.so")
 
@@ -97,4 +123,5 @@ def build_c_caller() -> str:
 
 if __name__ == "__main__":
     print(build(verbose="-v" in sys.argv))
+    print(build_marshal())
     print(build_c_caller())

@@ -61,12 +61,15 @@ class PRMOptimizer(torch.optim.Optimizer):
         self._adamw = None
         self.param_groups[0].setdefault("prm_step", 0)
 
-    def _state(self, p, names):
-        st = self.state[p]
-        for n in names:
-            if n not in st:
-                st[n] = torch.zeros(p.shape, dtype=torch.float32, device=p.device)
-        return [st[n] for n in names]
+    def _state(self, params, name):
+        state = self.state
+        try:
+            return [state[p][name] for p in params]
+        except KeyError:  # first step
+            for p in params:
+                if name not in state[p]:
+                    state[p][name] = torch.zeros(p.shape, dtype=torch.float32, device=p.device)
+            return [state[p][name] for p in params]
 
     @torch.no_grad()
     def step(self, closure=None):
@@ -80,13 +83,12 @@ class PRMOptimizer(torch.optim.Optimizer):
             grads = [p.grad for p in self._mats]
             if any(g is None for g in grads):
                 raise ValueError("every 2-D parameter needs a gradient at every step")
-            gcode = _dtype_code(grads, "gradients of the 2-D parameters")
             if self._prm is None:
+                gcode = _dtype_code(grads, "gradients of the 2-D parameters")
                 cfg = config_default(lr=float(g0["lr"]), param_dtype=self._wcode, grad_dtype=gcode,
                                      **self._prm_fields)
                 self._prm = Optimizer([tuple(p.shape) for p in self._mats], cfg)
-            M = [self._state(p, ("momentum",))[0] for p in self._mats]
-            self._prm.step(self._mats, grads, M, t, lr=float(g0["lr"]))
+            self._prm.step(self._mats, grads, self._state(self._mats, "momentum"), t, lr=float(g0["lr"]))
         if self._aux:
             agrads = [p.grad for p in self._aux]
             if any(g is None for g in agrads):
@@ -96,9 +98,8 @@ class PRMOptimizer(torch.optim.Optimizer):
                 cfg = adamw_config_default(lr=float(g0["aux_lr"]), param_dtype=self._acode, grad_dtype=gcode,
                                            **self._aux_fields)
                 self._adamw = AuxAdamW([p.numel() for p in self._aux], cfg)
-            mv = [self._state(p, ("exp_avg", "exp_avg_sq")) for p in self._aux]
             # AdamW's bias corrections count this optimizer's steps from 1
-            self._adamw.step(self._aux, agrads, [m for m, _ in mv], [v for _, v in mv], t + 1,
-                             lr=float(g0["aux_lr"]))
+            self._adamw.step(self._aux, agrads, self._state(self._aux, "exp_avg"), self._state(self._aux, "exp_avg_sq"),
+                             t + 1, lr=float(g0["aux_lr"]))
         g0["prm_step"] = t + 1
         return loss
