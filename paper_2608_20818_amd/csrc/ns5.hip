@@ -65,8 +65,8 @@ __global__ __launch_bounds__(256) void ns_prologue_kernel(const MatDesc* __restr
                                                           NsParams p) {
   using GT = typename NsStore<GD>::T;
   constexpr int T = kPrologueTile;  // 64
-  __shared__ uint16_t tile[T][T + 4];
-  __shared__ uint16_t tile_lo[HILO ? T : 1][T + 4];
+  __shared__ __attribute__((aligned(8))) uint16_t tile[T][T + 4];
+  __shared__ __attribute__((aligned(8))) uint16_t tile_lo[HILO ? T : 1][T + 4];
   __shared__ float red[4];
   const Item it = items[blockIdx.x];
   const MatDesc& d = md[it.mat];
@@ -83,13 +83,13 @@ __global__ __launch_bounds__(256) void ns_prologue_kernel(const MatDesc* __restr
   float* M = d.M;
   const bool vec = (n & 3) == 0;
   float ss = 0.f;
+  if (vec) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = tr + 16 * i;
-    const int64_t row = R0 + r, col = C0 + tc;
-    float u[4] = {0.f, 0.f, 0.f, 0.f};
-    if (row < m) {
-      if (vec && col + 3 < n) {
+    for (int i = 0; i < 4; ++i) {
+      const int r = tr + 16 * i;
+      const int64_t row = R0 + r, col = C0 + tc;
+      float u[4] = {0.f, 0.f, 0.f, 0.f};
+      if (row < m && col < n) {  // n is a multiple of 4
         float g[4], mm[4];
         VecNT<GT>::load4(G + row * n + col, g);
         VecNT<float>::load4(M + row * n + col, mm);
@@ -98,41 +98,74 @@ __global__ __launch_bounds__(256) void ns_prologue_kernel(const MatDesc* __restr
         VecNT<float>::store4(M + row * n + col, mm);
 #pragma unroll
         for (int k = 0; k < 4; ++k) u[k] = p.nesterov ? g[k] + p.beta * mm[k] : mm[k];
-      } else {
+      }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (col + k < n) {
-            const float g = VecNT<GT>::load1(G + row * n + col + k);
-            const float mm = p.beta * M[row * n + col + k] + p.gcoef * g;
-            M[row * n + col + k] = mm;
-            u[k] = p.nesterov ? g + p.beta * mm : mm;
-          }
+      for (int k = 0; k < 4; ++k) ss += u[k] * u[k];
+      const uint32_t h0 = f2bf(u[0]), h1 = f2bf(u[1]), h2 = f2bf(u[2]), h3 = f2bf(u[3]);
+      uint32_t l0 = 0, l1 = 0, l2 = 0, l3 = 0;
+      if constexpr (HILO) {
+        l0 = f2bf(u[0] - bf2f(h0));
+        l1 = f2bf(u[1] - bf2f(h1));
+        l2 = f2bf(u[2] - bf2f(h2));
+        l3 = f2bf(u[3] - bf2f(h3));
+      }
+      if (tall) {
+        *reinterpret_cast<uint2*>(XT + row * ld + col) = make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
+        if constexpr (HILO) *reinterpret_cast<uint2*>(d.XTl + row * ld + col) = make_uint2(l0 | (l1 << 16), l2 | (l3 << 16));
+      } else {
+        tile[r][tc + 0] = (uint16_t)h0;
+        tile[r][tc + 1] = (uint16_t)h1;
+        tile[r][tc + 2] = (uint16_t)h2;
+        tile[r][tc + 3] = (uint16_t)h3;
+        if constexpr (HILO) {
+          tile_lo[r][tc + 0] = (uint16_t)l0;
+          tile_lo[r][tc + 1] = (uint16_t)l1;
+          tile_lo[r][tc + 2] = (uint16_t)l2;
+          tile_lo[r][tc + 3] = (uint16_t)l3;
         }
       }
     }
+  } else {
+    // rows that start anywhere: a lane per column, so that a wave's access is one
+    // span of a row, and the loads of eight rows together (four elements of a row
+    // per lane, one by one, took 109 us for 15 M elements)
+    const int c = threadIdx.x & 63, r4 = threadIdx.x >> 6;
+    const int64_t col = C0 + c;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) ss += u[k] * u[k];
-    const uint32_t h0 = f2bf(u[0]), h1 = f2bf(u[1]), h2 = f2bf(u[2]), h3 = f2bf(u[3]);
-    uint32_t l0 = 0, l1 = 0, l2 = 0, l3 = 0;
-    if constexpr (HILO) {
-      l0 = f2bf(u[0] - bf2f(h0));
-      l1 = f2bf(u[1] - bf2f(h1));
-      l2 = f2bf(u[2] - bf2f(h2));
-      l3 = f2bf(u[3] - bf2f(h3));
+    for (int b = 0; b < T / 4; b += 8) {
+      float g[8], mm[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int64_t row = R0 + r4 + 4 * (b + q);
+        if (row < m && col < n) {
+          g[q] = VecNT<GT>::load1(G + row * n + col);
+          mm[q] = Vec<float>::load1(M + row * n + col);
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int r = r4 + 4 * (b + q);
+        const int64_t row = R0 + r;
+        float u = 0.f;
+        if (row < m && col < n) {
+          const float v = p.beta * mm[q] + p.gcoef * g[q];
+          Vec<float>::store1(M + row * n + col, v);
+          u = p.nesterov ? g[q] + p.beta * v : v;
+        }
+        ss += u * u;
+        const uint32_t h = f2bf(u);
+        tile[r][c] = (uint16_t)h;
+        if constexpr (HILO) tile_lo[r][c] = (uint16_t)f2bf(u - bf2f(h));
+      }
     }
     if (tall) {
-      *reinterpret_cast<uint2*>(XT + row * ld + col) = make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
-      if constexpr (HILO) *reinterpret_cast<uint2*>(d.XTl + row * ld + col) = make_uint2(l0 | (l1 << 16), l2 | (l3 << 16));
-    } else {
-      tile[r][tc + 0] = (uint16_t)h0;
-      tile[r][tc + 1] = (uint16_t)h1;
-      tile[r][tc + 2] = (uint16_t)h2;
-      tile[r][tc + 3] = (uint16_t)h3;
-      if constexpr (HILO) {
-        tile_lo[r][tc + 0] = (uint16_t)l0;
-        tile_lo[r][tc + 1] = (uint16_t)l1;
-        tile_lo[r][tc + 2] = (uint16_t)l2;
-        tile_lo[r][tc + 3] = (uint16_t)l3;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = tr + 16 * i;
+        *reinterpret_cast<uint2*>(XT + (R0 + r) * ld + C0 + tc) = *reinterpret_cast<const uint2*>(&tile[r][tc]);
+        if constexpr (HILO)
+          *reinterpret_cast<uint2*>(d.XTl + (R0 + r) * ld + C0 + tc) = *reinterpret_cast<const uint2*>(&tile_lo[r][tc]);
       }
     }
   }
@@ -156,15 +189,24 @@ __global__ __launch_bounds__(256) void ns_prologue_kernel(const MatDesc* __restr
   if (threadIdx.x == 0) d.partial[(int64_t)it.tm * d.ptiles_n + it.tn] = ss;
 }
 
-__global__ __launch_bounds__(256) void ns_alpha_kernel(const MatDesc* __restrict__ md,
-                                                       const int32_t* __restrict__ mats,
-                                                       NsParams p) {
-  __shared__ float red[4];
+// The loads of eight partial sums per thread together, 1024 threads a matrix: 7 us
+// for the 13824 partials of a 3072 x 18432 matrix, where 256 threads with one load
+// after the other took 27.
+__global__ __launch_bounds__(1024) void ns_alpha_kernel(const MatDesc* __restrict__ md,
+                                                        const int32_t* __restrict__ mats,
+                                                        NsParams p) {
+  __shared__ float red[16];
   const MatDesc& d = md[mats[blockIdx.x]];
   const int nt = d.ptiles_m * d.ptiles_n;
   float s = 0.f;
-  for (int i = threadIdx.x; i < nt; i += 256) s += d.partial[i];
-  s = block_sum<256>(s, red);
+  for (int i = threadIdx.x; i < nt; i += 8 * 1024) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = i + 1024 * k < nt ? Vec<float>::load1(d.partial + i + 1024 * k) : 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += v[k];
+  }
+  s = block_sum<1024>(s, red);
   if (threadIdx.x == 0) *d.alpha = 1.0f / (sqrtf(s) + p.eps_ns);
 }
 
@@ -925,7 +967,7 @@ hipError_t launch_ns_prologue(DType gt, const MatDesc* md, const Item* items, in
 hipError_t launch_ns_alpha(const MatDesc* md, const int32_t* mats, int32_t nmats,
                            const NsParams& p, hipStream_t s) {
   if (nmats <= 0) return hipSuccess;
-  ns_alpha_kernel<<<dim3(nmats), dim3(256), 0, s>>>(md, mats, p);
+  ns_alpha_kernel<<<dim3(nmats), dim3(1024), 0, s>>>(md, mats, p);
   return hipGetLastError();
 }
 
