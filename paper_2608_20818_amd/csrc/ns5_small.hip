@@ -9,8 +9,8 @@
 // or 128 instead of 256.
 //
 // One launch runs up to two products with a work list each (kind and operands
-// are run-time values), so that the factored and the plain group of a chunk,
-// which do not depend on each other, share their launches.
+// are run-time values): products of the factored and the plain group of a chunk,
+// which do not depend on each other, or two independent ones of a sequence.
 //
 // Eight waves, two per SIMD: two groups of 2 x 2 waves, each wave T/2 x T/2 of
 // the tile as 32 x 32 MFMA blocks, the groups splitting the k-steps of a stage
@@ -69,12 +69,12 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
   op.src = (opw >> 2) & 1;
   op.use_alpha = (opw >> 3) & 1;
   op.last = (opw >> 4) & 1;
-  op.sx = (opw >> 5) & 3;
-  op.sy = (opw >> 7) & 3;
-  op.so = (opw >> 9) & 3;
-  op.xshift = (opw >> 11) & 1 ? sp.a : 0.f;
-  op.yshift = (opw >> 12) & 1 ? sp.a : 0.f;
-  const bool hilo = (opw >> 13) & 1;
+  op.sx = (opw >> 5) & 7;
+  op.sy = (opw >> 8) & 7;
+  op.so = (opw >> 11) & 7;
+  op.xshift = (opw >> 14) & 1 ? sp.a : 0.f;
+  op.yshift = (opw >> 15) & 1 ? sp.a : 0.f;
+  const bool hilo = (opw >> 16) & 1;
   const MatDesc& d = md[it.mat];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -551,8 +551,8 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
 // reading its arguments from host memory.
 static uint32_t ns_pack(const NsOp& o, int hilo) {
   return (uint32_t)o.kind | (uint32_t)o.src << 2 | (uint32_t)o.use_alpha << 3 | (uint32_t)o.last << 4 |
-         (uint32_t)o.sx << 5 | (uint32_t)o.sy << 7 | (uint32_t)o.so << 9 | (uint32_t)(o.xshift != 0) << 11 |
-         (uint32_t)(o.yshift != 0) << 12 | (uint32_t)(hilo != 0) << 13;
+         (uint32_t)o.sx << 5 | (uint32_t)o.sy << 8 | (uint32_t)o.so << 11 | (uint32_t)(o.xshift != 0) << 14 |
+         (uint32_t)(o.yshift != 0) << 15 | (uint32_t)(hilo != 0) << 16;
 }
 
 hipError_t launch_ns_small(int tile, const MatDesc* md, const Item* items0, int32_t n0, const NsOp& op0,

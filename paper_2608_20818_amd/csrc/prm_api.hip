@@ -593,6 +593,11 @@ void fill_descs(const Plan& P, char* chunk_base, char* small_base, char* tall_ba
       d.S[k] = k < ns ? (uint16_t*)(w + nx * xs + k * gs) : nullptr;
       d.dS[k] = k < ns ? (float*)(w + nx * xs + ns * gs + k * vs) : nullptr;
     }
+    // the factored form needs a fifth split matrix on small tiles; rp x rp bf16
+    // and rp fp32 fit an iterate's region: cp > rp, or both are 64 in one of 256 x 256
+    const bool fifth = P.chain[i] && P.tile != kNsTile;
+    d.S[4] = fifth ? d.XT : nullptr;
+    d.dS[4] = fifth ? (float*)(d.XT + d.rp * d.rp) : nullptr;
     d.ptiles_m = (int32_t)((d.tall ? d.cp : d.rp) / kPrologueTile);
     d.ptiles_n = (int32_t)((d.tall ? d.rp : d.cp) / kPrologueTile);
     d.partial = (float*)(small_base + P.small_off[i]);
@@ -804,14 +809,18 @@ std::vector<NsLaunch> plain_sequence(const NsGroup& G, float a) {
 //   j = 2: A2 (S0) = X2 X2^T, B2 (S1)
 //   j = 3: P2^2 (S2), A3 = P2^2 A2 (S3), B3 (S0), Q = P3 P2 (S2)
 //   j = 4: P3^2 (S1), A4 = P3^2 A3 (S0), B4 (S1), Q = P4 Q (S3); X5 = Q X2
-std::vector<NsLaunch> chain_sequence(const NsGroup& G, float a) {
+// On small tiles P3^2 goes to S4, so that it does not depend on Q = P3 P2 before
+// it (products kChainPair and the next share a launch).
+constexpr size_t kChainPair = 12;
+std::vector<NsLaunch> chain_sequence(const NsGroup& G, float a, bool small) {
+  const int sq = small ? 4 : 1;
   return {op_gram(G, 0, 1, 0),           op_poly(G, 0, 1),
           op_sprod(G, 1, a, 1, a, 2),    op_sprod(G, 2, 0.f, 0, 0.f, 3), op_poly(G, 3, 0),
           op_sprod(G, 0, a, 1, a, 2),    op_apply(G, 0, 1, 2, 0.f, 0),
           op_gram(G, 1, 0, 0),           op_poly(G, 0, 1),
           op_sprod(G, 1, a, 1, a, 2),    op_sprod(G, 2, 0.f, 0, 0.f, 3), op_poly(G, 3, 0),
           op_sprod(G, 0, a, 1, a, 2),
-          op_sprod(G, 0, a, 0, a, 1),    op_sprod(G, 1, 0.f, 3, 0.f, 0), op_poly(G, 0, 1),
+          op_sprod(G, 0, a, 0, a, sq),   op_sprod(G, sq, 0.f, 3, 0.f, 0), op_poly(G, 0, 1),
           op_sprod(G, 1, a, 2, 0.f, 3),  op_apply(G, 1, 0, 3, 0.f, 1)};
 }
 
@@ -847,7 +856,7 @@ int refresh_step(prm_ctx* c, float lr, bool debug) {
       return launch_ns_alpha(md, c->d_ints + ch.off_mats, (int32_t)ch.mats.size(), p, c->stream);
     });
     if (rc) return rc;
-    std::vector<NsLaunch> plain = plain_sequence(ch.plain, a), chain = chain_sequence(ch.chain, a);
+    std::vector<NsLaunch> plain = plain_sequence(ch.plain, a), chain = chain_sequence(ch.chain, a, P.tile != kNsTile);
     if (ch.plain.mats.empty()) plain.clear();
     if (ch.chain.mats.empty()) chain.clear();
     auto list_of = [&](const NsLaunch& l) { return c->d_items + (l.op.kind == GEMM_APPLY ? l.G->off_apply : l.G->off_upper); };
@@ -881,17 +890,20 @@ int refresh_step(prm_ctx* c, float lr, bool debug) {
         return launch_ns_gemm((GemmKind)l.op.kind, wt, md, list_of(l), count_of(l), p, c->stream, hilo);
       }, exec);
     };
-    // the two groups are independent: on small tiles, the k-th products of both
-    // share a launch (each has its own when profiling)
-    for (size_t k = 0; k < std::max(plain.size(), chain.size()); ++k) {
-      const NsLaunch* x = k < chain.size() ? &chain[k] : nullptr;
-      const NsLaunch* y = k < plain.size() ? &plain[k] : nullptr;
-      if (x && y && !c->prof && P.tile != kNsTile) {
-        if ((rc = run(*x, y))) return rc;
-        continue;
+    // On small tiles, products that do not depend on each other share a launch:
+    // those of the two groups, and one pair of the factored sequence.  (Each has
+    // its own when profiling.)
+    const bool pairs = P.tile != kNsTile && !c->prof;
+    for (size_t x = 0, y = 0; x < chain.size() || y < plain.size();) {
+      if (pairs && x == kChainPair && x < chain.size()) {
+        if ((rc = run(chain[x], &chain[x + 1]))) return rc;
+        x += 2;
+      } else if (pairs && x < chain.size() && y < plain.size()) {
+        if ((rc = run(chain[x++], &plain[y++]))) return rc;
+      } else {
+        if (x < chain.size() && (rc = run(chain[x++], nullptr))) return rc;
+        if (y < plain.size() && (rc = run(plain[y++], nullptr))) return rc;
       }
-      if (x && (rc = run(*x, nullptr))) return rc;
-      if (y && (rc = run(*y, nullptr))) return rc;
     }
   }
   return PRM_OK;

@@ -34,8 +34,10 @@ struct MatDesc {
   // diagonal.  The dispatcher assigns them roles (the Gram matrix A, B =
   // bA + cA^2, and for the chained path the products of the factors aI + B);
   // matrices on the plain five-iteration path use S[0], S[1] only.
-  uint16_t* S[4];
-  float* dS[4];
+  // S[4] (small tiles, factored form) lies over XT, which is free after the
+  // first apply.
+  uint16_t* S[5];
+  float* dS[5];
   float* partial; // prologue: one sum of squares per 64 x 64 tile
   float* alpha;   // 1 / (||U||_F + eps_ns)
   int64_t rp, cp;
