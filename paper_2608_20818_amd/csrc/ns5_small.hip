@@ -86,14 +86,17 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
   const uint16_t* XTcl = op.src == 0 ? d.XTl : d.XTnl;  // precise mode: low parts
   const int64_t row0 = (int64_t)it.tm * T, col0 = (int64_t)it.tn * T;
 
-  // operands of K segment 0; in precise mode the Gram sums hi hi^T + hi lo^T +
-  // lo hi^T over three segments and the apply hi Q + lo Q over two
+  // Operands of K segment 0; in precise mode the apply sums hi Q + lo Q over two
+  // segments.  The Gram's hi hi^T + hi lo^T + lo hi^T (`tri`) come from one pass: a
+  // stage holds 32 k-rows of four panels, hi and lo of the tile's rows, then of its
+  // columns (each loaded once for the products it is in, where three segments
+  // would load six).
   const uint16_t *P, *Q;
   int nk, nseg = 1;
+  const bool tri = tn && hilo;
   if (kind == GEMM_GRAM) {
     P = XTc; Q = XTc;
-    nk = (int)(d.cp / BK);
-    if (hilo) nseg = 3;
+    nk = (int)(d.cp / (tri ? BK / 2 : BK));
   } else {
     P = kind == GEMM_APPLY ? XTc : d.S[op.sx];
     Q = d.S[op.sy];
@@ -118,11 +121,11 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
     voff[0] = (uint32_t)(lane >> 3) * ldb + (((lane & 7) ^ (lane >> 4) ^ (4 * (wave * LPO & 1))) << 4);
     voff[1] = voff[0] ^ 64;  // ldb is a multiple of 128
   }
-  const uint64_t qstep = (uint64_t)(tn ? 512 / T : 8) * ldb;             // between a wave's loads
-  const uint64_t kstep = tn ? (uint64_t)BK * ldb : (uint64_t)BK * 2;     // between stages
-  const uint64_t offA = (tn ? (uint64_t)row0 * 2 : (uint64_t)row0 * ldb) + (uint64_t)(wave * LPO) * qstep;
-  const uint64_t offB = (tn ? (uint64_t)col0 * 2 : (uint64_t)col0 * ldb) + (uint64_t)(wave * LPO) * qstep;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)lds + (uint32_t)(wave * LPO) * 1024u;
+  const uint64_t lrows = (uint64_t)(tn ? 512 / T : 8) * ldb;              // of one load
+  const uint64_t kstep = tn ? (uint64_t)(tri ? BK / 2 : BK) * ldb : (uint64_t)BK * 2;  // between stages
+  const uint64_t offA = (tn ? (uint64_t)row0 * 2 : (uint64_t)row0 * ldb) + (uint64_t)(wave * LPO) * lrows;
+  const uint64_t offB = (tn ? (uint64_t)col0 * 2 : (uint64_t)col0 * ldb) + (uint64_t)(wave * LPO) * lrows;
+  constexpr int PANEL = OP_BYTES / 2;  // of the four of a `tri` stage; two waves load each
   auto uniform64 = [](uint64_t u) __attribute__((always_inline)) {
     return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32) |
            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
@@ -130,8 +133,21 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
   // Where the wave's loads of the next stage to be issued start: operand
   // addresses and LDS destination; moves on with every stage.
   uint64_t srcA = uniform64((uint64_t)(uintptr_t)P + offA), srcB = uniform64((uint64_t)(uintptr_t)Q + offB);
+  uint64_t qstep = lrows;                                     // between loads q and q + 2
+  uint32_t lds0 = wave * LPO * 1024, dstB = OP_BYTES, dstq = 1024;  // of load 0, of odd loads, between q and q + 2
+  if (tri) {
+    const int panel = wave >> 1, first = (wave & 1) * LPS;
+    const uint16_t* src = (panel & 1 ? XTcl : XTc) + (panel & 2 ? col0 : row0);
+    srcA = uniform64((uint64_t)(uintptr_t)src + first * lrows);
+    srcB = srcA + lrows;
+    qstep = 2 * lrows;
+    lds0 = panel * PANEL + first * 1024;
+    dstB = 1024;
+    dstq = 2048;
+  }
+  lds0 += (uint32_t)(uintptr_t)(lds_ptr)lds;
   int istage = 0, ibuf = 0;
-  // One of the wave's 2 LPO loads of that stage (even q: first operand).
+  // One of the wave's LPS loads of that stage (even q: first operand).
   // Assembly, so that the compiler does not wait for the loads at every LDS
   // read; it sees neither the LDS writes nor their wait, which are explicit
   // below.  The s_nop is the wait state an M0 write needs before a load into
@@ -142,7 +158,7 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
     const int qq = q >> 1;
     const uint64_t src = ((q & 1) ? srcB : srcA) + qq * qstep;
     const uint32_t dst = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + (uint32_t)ibuf * STAGE_BYTES)) +
-                         ((q & 1) ? OP_BYTES : 0) + qq * 1024;
+                         ((q & 1) ? dstB : 0) + qq * dstq;
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"  // the M0 clobber, see above
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff[qq & 1]), "s"(src), "s"(dst) : "m0");
@@ -153,17 +169,9 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
     ibuf = ibuf + 1 == NST ? 0 : ibuf + 1;
     srcA += kstep;
     srcB += kstep;
-    if (nseg > 1 && (istage == nk || istage == 2 * nk)) {  // the next K segment
-      const uint16_t* pa = P;
-      const uint16_t* pb = Q;
-      if (tn) {
-        pa = istage == nk ? XTc : XTcl;
-        pb = istage == nk ? XTcl : XTc;
-      } else {
-        pa = XTcl;
-      }
-      srcA = uniform64((uint64_t)(uintptr_t)pa + offA);
-      srcB = uniform64((uint64_t)(uintptr_t)pb + offB);
+    if (nseg > 1 && istage == nk) {  // the next K segment
+      srcA = uniform64((uint64_t)(uintptr_t)XTcl + offA);
+      srcB = uniform64((uint64_t)(uintptr_t)Q + offB);
     }
   };
 
@@ -224,7 +232,11 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
   // While the previous stage's products run from one register set, the stage's
   // fragments are read into the other and the loads are issued, spread between
   // the products: one wave per SIMD has nothing else to hide them behind.
-  auto main_loop = [&](auto rd_a, auto rd_b) __attribute__((always_inline)) {
+  // NP = 3 (`tri`): the two fragment sets are hi and lo of one k-step, and the
+  // products hi hi, hi lo and lo hi; otherwise they are the group's two k-steps.
+  auto main_loop = [&](auto rd_a, auto rd_b, auto npc) __attribute__((always_inline)) {
+    constexpr int NP = decltype(npc)::value;
+    static_assert(KSG == 2, "two fragment sets");
     bf16x8 fa[2][KSG][MI], fb[2][KSG][MI];
     int buf = 0;
     // stage s into set `setc`; PREV: with the previous stage's products; MORE:
@@ -240,7 +252,7 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
       __syncthreads();
       const char* a = lds + buf * STAGE_BYTES;
       const char* b = a + OP_BYTES;
-      constexpr int G = KSG * MI * MI, F = 2 * KSG * MI;  // products; F fragment reads and LPS loads are spread over them
+      constexpr int G = NP * MI * MI, F = 2 * KSG * MI;  // products; F fragment reads and LPS loads are spread over them
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         if (more) {
@@ -256,7 +268,8 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
         // operands swapped: accumulates the transposed block (P Q^T)^T = Q P^T
         if constexpr (PREV) {
           const int ks = g / (MI * MI), i = (g / MI) % MI, j = g % MI;
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set ^ 1][ks][j], fa[set ^ 1][ks][i], acc[i][j], 0, 0, 0);
+          const int ka = NP == 3 ? ks >> 1 : ks, kb = NP == 3 ? ks & 1 : ks;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set ^ 1][kb][j], fa[set ^ 1][ka][i], acc[i][j], 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -266,12 +279,14 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
     auto products = [&](auto setc) __attribute__((always_inline)) {
       constexpr int set = decltype(setc)::value;
 #pragma unroll
-      for (int ks = 0; ks < KSG; ++ks)
+      for (int ks = 0; ks < NP; ++ks)
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < MI; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][ks][j], fa[set][ks][i], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < MI; ++j) {
+            const int ka = NP == 3 ? ks >> 1 : ks, kb = NP == 3 ? ks & 1 : ks;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][kb][j], fa[set][ka][i], acc[i][j], 0, 0, 0);
+          }
     };
     constexpr std::integral_constant<int, 0> set0{};
     constexpr std::integral_constant<int, 1> set1{};
@@ -304,18 +319,26 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
-        const int kr = 16 * KSG * kg + 8 * (g >> 1) + 4 * kk + (jl >> 2);
+        const int kr = 16 * (tri ? 1 : KSG) * kg + 8 * (g >> 1) + 4 * kk + (jl >> 2);
         const int ca = wm * WT + i * 32 + 16 * (g & 1) + 4 * (jl & 3), cb = wn * WT + i * 32 + 16 * (g & 1) + 4 * (jl & 3);
         oa[i][kk] = kr * (2 * T) + (((ca >> 3) ^ sw) << 4) + ((ca & 7) << 1);
         ob[i][kk] = kr * (2 * T) + (((cb >> 3) ^ sw) << 4) + ((cb & 7) << 1);
       }
-    auto rd = [&](const char* base, const int (&off)[2], int ks) __attribute__((always_inline)) {
-      const v4i16 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(base + off[0] + ks * 16 * (2 * T)));
-      const v4i16 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(base + off[1] + ks * 16 * (2 * T)));
+    // `set` apart: the next k-step, or the low part's panel
+    auto rd = [&](const char* base, const int (&off)[2], int set) __attribute__((always_inline)) {
+      const v4i16 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(base + off[0] + set));
+      const v4i16 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16)(base + off[1] + set));
       return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
     };
-    main_loop([&](const char* base, int i, int ks) __attribute__((always_inline)) { return rd(base, oa[i], ks); },
-              [&](const char* base, int i, int ks) __attribute__((always_inline)) { return rd(base, ob[i], ks); });
+    if (tri)
+      main_loop([&](const char* base, int i, int ks) __attribute__((always_inline)) { return rd(base, oa[i], ks * PANEL); },
+                [&](const char* base, int i, int ks) __attribute__((always_inline)) { return rd(base, ob[i], ks * PANEL); },
+                std::integral_constant<int, 3>{});
+    else
+      main_loop(
+          [&](const char* base, int i, int ks) __attribute__((always_inline)) { return rd(base, oa[i], ks * 32 * T); },
+          [&](const char* base, int i, int ks) __attribute__((always_inline)) { return rd(base, ob[i], ks * 32 * T); },
+          std::integral_constant<int, KSG>{});
   } else {
     const int arow = wm * WT + m, brow = wn * WT + m;
     int oa[KSG], ob[KSG];
@@ -328,7 +351,8 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
     main_loop([&](const char* base, int i, int ks) __attribute__((always_inline)) {
                 return *reinterpret_cast<const bf16x8*>(base + oa[ks] + i * 32 * 128); },
               [&](const char* base, int i, int ks) __attribute__((always_inline)) {
-                return *reinterpret_cast<const bf16x8*>(base + ob[ks] + i * 32 * 128); });
+                return *reinterpret_cast<const bf16x8*>(base + ob[ks] + i * 32 * 128); },
+              std::integral_constant<int, KSG>{});
   }
 
   // ---- epilogue ----

@@ -252,7 +252,7 @@ void choose_tile(Plan& P) {
       const double r = (double)round_up(std::min(P.m[i], P.nn[i]), pr.tile);
       const double c = (double)round_up(std::max(P.m[i], P.nn[i]), pr.tile);
       const double tr = r / pr.tile, tc = c / pr.tile;
-      const double time[3] = {c / 64 * (P.precise ? 3 : 1) * pr.stage + pr.fixed, r / 64 * pr.stage + pr.fixed,
+      const double time[3] = {c / 64 * (P.precise ? (pr.tile == 256 ? 3 : 2) : 1) * pr.stage + pr.fixed, r / 64 * pr.stage + pr.fixed,
                               r / 64 * (P.precise ? 2 : 1) * pr.stage + pr.fixed};
       const double tiles[3] = {tr * (tr + 1) / 2, tr * (tr + 1) / 2, tr * tc};
       for (int k = 0; k < 3; ++k) {
