@@ -104,15 +104,16 @@ struct WideClass {
 };
 
 // The matrices of a chunk that run the same NS5 sequence, with their tile
-// lists: `upper` for the symmetric r x r results (Gram, square, split
-// products), `apply` for the tiles of X'^T.  Per launch over the group:
+// lists: `gram` and `upper` for the symmetric r x r results (over K = c, and
+// over K = r: square, split products), `apply` for the tiles of X'^T.  Per
+// launch over the group:
 // algorithmic FLOPs of an r x r times r x c product (Gram, apply) and of an
 // r x r product, and the executed FLOPs of each kind.
 struct NsGroup {
   std::vector<int32_t> mats;
-  std::vector<Item> upper, apply;
-  size_t off_upper = 0, off_apply = 0;
-  int32_t n_upper = 0, n_apply = 0;  // work groups of a launch (list lengths)
+  std::vector<Item> gram, upper, apply;
+  size_t off_gram = 0, off_upper = 0, off_apply = 0;
+  int32_t n_gram = 0, n_upper = 0, n_apply = 0;  // work groups of a launch (list lengths)
   double elems = 0, alg_rc = 0, alg_rr = 0, exec_gram = 0, exec_rr = 0, exec_apply = 0;
 };
 
@@ -229,16 +230,18 @@ void wide_class(int64_t n, int& tpr, int& nch) {
 constexpr int kOwnNormBlocks = 64;
 
 // Tile edge of the plan's NS5 products: 256 runs its MFMAs best, smaller tiles
-// spread a small set over more CUs and pad less.  Each product is priced as if
-// every matrix ran in one launch over the chip's 256 CUs: all tiles' time over
-// 256 plus half the longest tile (the uneven end), but no less than the longest.
+// spread a small set over more CUs and pad less.  A launch over the chip's 256 CUs
+// is priced as all its tiles' time over 256 plus half the longest tile (the uneven
+// end), but no less than the longest.  At 256 the plain and the factored group have
+// launches of their own; on small tiles they are priced as sharing every one.
 // A tile costs its K / 64 stages plus a fixed part, in us as measured (a stage
 // of 64 moves 16, 32 or 64 KB into LDS, at 31 to 39 bytes per clock and CU).
 // Measured refresh, us at 64 / 128 / 256, the choice first: six matrices with
 // r <= 256: 100 / 153 / 580; ten with r = 384 (three steps): 294 / 322 / 980;
 // seven with r <= 1001: 128: 550, 559 / 1500; five with r = 1024, precise: 128:
 // 1168, 1410 / 2430; one 2048 x 6144: 128: 522, 667 / 1060; 15 with r = 2048:
-// 256: 5700, 8831 / 6695.
+// 256: 5700, 8831 / 6695; 25 with r = 768: 128: 1103, 1105 / 1471; 25 with r = 1600:
+// 256: 6269, though 128 took 5956.
 void choose_tile(Plan& P) {
   struct Price { int tile; double stage, fixed; };
   constexpr Price price[3] = {{256, 1.17, 9.0}, {128, 0.42, 5.0}, {64, 0.16, 3.5}};
@@ -247,7 +250,7 @@ void choose_tile(Plan& P) {
   for (const Price& pr : price) {
     // Gram, r x r products, apply: time of all tiles, of the longest, launches
     // over the set (mean; the factored form runs 2, 14, 2, the plain one 5 each)
-    double total[3] = {0, 0, 0}, longest[3] = {0, 0, 0}, count[3] = {0, 0, 0}, est = 0;
+    struct Cost { double total[3], longest[3], count[3]; int mats; } cost[2] = {};
     for (int i = 0; i < P.n; ++i) {
       const double r = (double)round_up(std::min(P.m[i], P.nn[i]), pr.tile);
       const double c = (double)round_up(std::max(P.m[i], P.nn[i]), pr.tile);
@@ -255,13 +258,18 @@ void choose_tile(Plan& P) {
       const double time[3] = {c / 64 * (P.precise ? (pr.tile == 256 ? 3 : 2) : 1) * pr.stage + pr.fixed, r / 64 * pr.stage + pr.fixed,
                               r / 64 * (P.precise ? 2 : 1) * pr.stage + pr.fixed};
       const double tiles[3] = {tr * (tr + 1) / 2, tr * (tr + 1) / 2, tr * tc};
+      Cost& g = cost[pr.tile == kNsTile && P.chain[i]];
+      ++g.mats;
       for (int k = 0; k < 3; ++k) {
-        total[k] += tiles[k] * time[k];
-        longest[k] = std::max(longest[k], time[k]);
-        count[k] += (P.chain[i] ? (k == 1 ? 14.0 : 2.0) : 5.0) / P.n;
+        g.total[k] += tiles[k] * time[k];
+        g.longest[k] = std::max(g.longest[k], time[k]);
+        g.count[k] += P.chain[i] ? (k == 1 ? 14.0 : 2.0) : 5.0;
       }
     }
-    for (int k = 0; k < 3; ++k) est += count[k] * std::max(longest[k], total[k] / kCus + 0.5 * longest[k]);
+    double est = 0;
+    for (const Cost& g : cost)
+      for (int k = 0; k < 3 && g.mats; ++k)
+        est += g.count[k] / g.mats * std::max(g.longest[k], g.total[k] / kCus + 0.5 * g.longest[k]);
     if (pr.tile == 256 || est < best) {
       best = est;
       P.tile = pr.tile;
@@ -491,10 +499,11 @@ void build_lists(Plan& P, bool items) {
     for (int grp = 0; grp < 2; ++grp) {
       NsGroup& G = grp ? ch.chain : ch.plain;
       // symmetric products: whole matrices per XCD where that balances (their
-      // tiles share the r x r panels in the XCD's L2).  Apply: an eighth of each
+      // tiles share the r x r panels in the XCD's L2); the Gram's K is c, that of
+      // the others r, so each has its own balance.  Apply: an eighth of each
       // matrix per XCD, so all XCDs stream the same factor at the same time (it
       // is read by every tile row; the last-level cache serves the repeats).
-      XcdLists u(1), a(kXcds);
+      XcdLists g(1), u(1), a(kXcds);
       std::vector<Item> tiles;
       for (int i : ch.mats) {
         if (P.chain[i] != grp) continue;
@@ -513,20 +522,24 @@ void build_lists(Plan& P, bool items) {
         G.exec_apply += (double)tc * tr * 2 * t2 * rp * (P.tile == kNsTile ? 1.0 + kNsTile / 4.0 / rp : 1.0);
         if (!items) {
           G.n_upper += tr * (tr + 1) / 2;
+          G.n_gram = G.n_upper;
           G.n_apply += tc * tr;
           continue;
         }
         tiles.clear();
         tile_order(i, tr, tr, true, tiles);
-        u.add(tiles, cp);
+        g.add(tiles, cp);
+        u.add(tiles, rp);
         // tiles of X'^T: rows over c, columns over r
         tiles.clear();
         tile_order(i, tc, tr, false, tiles);
         a.add(tiles, rp);
       }
       if (!items) continue;
+      G.gram = g.interleaved();
       G.upper = u.interleaved();
       G.apply = a.interleaved();
+      G.n_gram = (int32_t)G.gram.size();
       G.n_upper = (int32_t)G.upper.size();
       G.n_apply = (int32_t)G.apply.size();
     }
@@ -559,6 +572,7 @@ void build_lists(Plan& P, bool items) {
     ch.off_mats = put_ints(ch.mats);
     ch.off_prologue = put_items(ch.prologue);
     for (NsGroup* G : {&ch.plain, &ch.chain}) {
+      G->off_gram = put_items(G->gram);
       G->off_upper = put_items(G->upper);
       G->off_apply = put_items(G->apply);
     }
@@ -859,8 +873,14 @@ int refresh_step(prm_ctx* c, float lr, bool debug) {
     std::vector<NsLaunch> plain = plain_sequence(ch.plain, a), chain = chain_sequence(ch.chain, a, P.tile != kNsTile);
     if (ch.plain.mats.empty()) plain.clear();
     if (ch.chain.mats.empty()) chain.clear();
-    auto list_of = [&](const NsLaunch& l) { return c->d_items + (l.op.kind == GEMM_APPLY ? l.G->off_apply : l.G->off_upper); };
-    auto count_of = [&](const NsLaunch& l) { return l.op.kind == GEMM_APPLY ? l.G->n_apply : l.G->n_upper; };
+    auto list_of = [&](const NsLaunch& l) {
+      const NsGroup& G = *l.G;
+      return c->d_items + (l.op.kind == GEMM_APPLY ? G.off_apply : l.op.kind == GEMM_GRAM ? G.off_gram : G.off_upper);
+    };
+    auto count_of = [&](const NsLaunch& l) {
+      const NsGroup& G = *l.G;
+      return l.op.kind == GEMM_APPLY ? G.n_apply : l.op.kind == GEMM_GRAM ? G.n_gram : G.n_upper;
+    };
     // one product, or two of independent groups (l1) in one small-tile launch
     auto run = [&](const NsLaunch& l, const NsLaunch* l1) {
       const NsGroup& G = *l.G;
@@ -1523,6 +1543,7 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
     ok = ch.n_prologue == pm * pn && G.n_upper == T * (T + 1) / 2 && G.n_apply == tc * T &&
          add(ch.off_prologue, ch.n_prologue, pn, 0) && add(G.off_upper, G.n_upper, T, 1) &&
          add(G.off_apply, G.n_apply, T, 0);
+    G.off_gram = G.off_upper;  // one matrix: one order of its tiles serves both
   } else if (P.tall[0]) {
     const int32_t nt = P.n_tall4 + P.n_tall1;
     ok = nt == P.nrb[0] * slabs && P.n_fin == fins && add(P.n_tall4 ? P.off_tall4 : P.off_tall1, nt, slabs, 0) &&
