@@ -295,9 +295,10 @@ int prm_peak_hbm(void* hip_stream, uint64_t bytes, double* read_gbs, double* wri
  *
  * Scratch: the descriptor, work lists and workspace (the NS5 iterates and Gram
  * factors on refresh steps, a tall matrix's column statistics on row-wise
- * steps) live in one static device array of PRM_NOALLOC_SCRATCH_BYTES per GPU,
- * which the library holds on every GPU it runs on until the process ends.  A
- * step that needs more is refused with PRM_ENOMEM before anything is enqueued
+ * steps) live in one static device array of PRM_NOALLOC_SCRATCH_BYTES (and 512 KiB
+ * for long work lists) per GPU, which the library holds on every GPU it runs on until
+ * the process ends.  A step that needs more is refused with PRM_ENOMEM before anything
+ * is enqueued
  * (a refresh step needs 4 rp cp + 8 rp^2 bytes in the factored form, c >= 2r,
  * and 4 rp cp + 4 rp^2 otherwise, with rp x cp the oriented shape padded to
  * 256 (whatever the tile it runs on): 3072 x 12288 and 5120 x 5120 fit, 3072 x 18432 does not; row-wise steps of wide

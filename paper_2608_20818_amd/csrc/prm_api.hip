@@ -1012,9 +1012,48 @@ int check_adamw_config(const prm_adamw_config* c) {
 // hipGetSymbolAddress (taken once per device, with that device current) and
 // is the only handle host code passes on.
 // ---------------------------------------------------------------------------
-static __device__ __align__(256) char scratch[PRM_NOALLOC_SCRATCH_BYTES];
+// What a step needs is priced with work lists for 256-wide pieces (prm.h); lists
+// for smaller pieces may take kNoallocListBytes more, which the limit does not
+// count.  At most: 46341 / 32 column slabs of the finalize (a tall matrix's
+// statistics, n^2 / 8 bytes or more, fit the limit) and, as 4 rp cp + 4 rp^2 <=
+// 2^28, 2^26 / 64^2 tiles of an apply and 91 (91 + 1) / 2 of a symmetric product,
+// 16 bytes each.
+constexpr uint64_t kNoallocListBytes = 512ull << 10;
+static __device__ __align__(256) char scratch[PRM_NOALLOC_SCRATCH_BYTES + kNoallocListBytes];
 
 namespace {
+
+// Where the parts of one call lie in the scratch array: descriptor | int lists |
+// work lists | per-matrix scalars | NS5 workspace (refresh) or tall column
+// statistics (row-wise).
+struct NoallocLayout {
+  int64_t T = 0, tc = 0, pn = 0, pm = 0, slabs = 0, fins = 0;
+  int64_t nitems = 0;
+  uint64_t off_ints = 0, off_items = 0, off_small = 0, off_big = 0;
+  uint64_t priced = 0;  // bytes held against the limit
+  uint64_t end = 0;     // bytes laid out
+  NoallocLayout() = default;
+  NoallocLayout(const Plan& P, int rho) {
+    T = P.rp[0] / P.tile;
+    tc = P.cp[0] / P.tile;
+    pn = (P.tall[0] ? P.rp[0] : P.cp[0]) / kPrologueTile;
+    pm = (P.tall[0] ? P.cp[0] : P.rp[0]) / kPrologueTile;
+    slabs = (P.nn[0] + 255) / 256;
+    fins = (P.nn[0] + kFinCols - 1) / kFinCols;
+    const int64_t tiles = (int64_t)P.nrb[0] * slabs;
+    nitems = rho ? pm * pn + T * (T + 1) / 2 + tc * T : (P.tall[0] ? tiles + fins : 0);
+    off_ints = align256(sizeof(MatDesc));
+    off_items = off_ints + 256;
+    const uint64_t big = rho ? P.chunk_bytes : P.tall_bytes;
+    auto behind_items = [&](int64_t n) {
+      return off_items + align256((uint64_t)std::max<int64_t>(n, 1) * sizeof(Item));
+    };
+    off_small = behind_items(nitems);
+    off_big = off_small + align256(P.small_bytes);
+    end = off_big + big;
+    priced = behind_items(rho ? nitems : (P.tall[0] ? tiles + slabs : 0)) + align256(P.small_bytes) + big;
+  }
+};
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -1033,6 +1072,21 @@ int noalloc_scratch(int dev, char** out) {
     g_scratch_ptr[dev] = static_cast<char*>(p);
   }
   *out = g_scratch_ptr[dev];
+  return PRM_OK;
+}
+
+// Plan and layout of step `step` of one matrix.
+int noalloc_plan(const prm_config* cfg, int64_t rows, int64_t cols, int64_t step, Plan& P, NoallocLayout& L) {
+  int rc = make_plan(1, &rows, &cols, cfg, P);
+  if (rc) return rc;
+  const int rho = refresh_of(*cfg, step);
+  L = NoallocLayout(P, rho);
+  if (L.priced > PRM_NOALLOC_SCRATCH_BYTES && P.tile != kNsTile) {
+    // smaller tiles have longer work lists; what fits on the largest one is taken
+    rc = make_plan(1, &rows, &cols, cfg, P, kNsTile);
+    if (rc) return rc;
+    L = NoallocLayout(P, rho);
+  }
   return PRM_OK;
 }
 
@@ -1477,7 +1531,8 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   prm_config c2 = *cfg;
   c2.workspace_budget_bytes = 1ull << 62;
   Plan P;
-  int rc = make_plan(1, &rows, &cols, &c2, P);
+  NoallocLayout L;
+  int rc = noalloc_plan(&c2, rows, cols, step, P, L);
   if (rc) return rc;
   const void* ps[3] = {param, grad, momentum};
   for (int k = 0; k < 3; ++k) {
@@ -1491,36 +1546,11 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
     if (rc) return rc;
   }
   const int rho = refresh_of(c2, step);
-  // scratch layout: descriptor | int lists | work lists | per-matrix scalars |
-  // NS5 workspace (refresh) or tall column statistics (row-wise)
-  int64_t T, tc, pn, pm, slabs, fins;
-  uint64_t off_ints, off_items, off_small, off_big, need;
-  auto layout = [&]() {
-    T = P.rp[0] / P.tile;
-    tc = P.cp[0] / P.tile;
-    pn = (P.tall[0] ? P.rp[0] : P.cp[0]) / kPrologueTile;
-    pm = (P.tall[0] ? P.cp[0] : P.rp[0]) / kPrologueTile;
-    slabs = (P.nn[0] + 255) / 256;
-    fins = (P.nn[0] + kFinCols - 1) / kFinCols;
-    const int64_t n = rho ? pm * pn + T * (T + 1) / 2 + tc * T : (P.tall[0] ? (int64_t)P.nrb[0] * slabs + fins : 0);
-    off_ints = align256(sizeof(MatDesc));
-    off_items = off_ints + 256;
-    off_small = off_items + align256((uint64_t)std::max<int64_t>(n, 1) * sizeof(Item));
-    off_big = off_small + align256(P.small_bytes);
-    need = off_big + (rho ? P.chunk_bytes : P.tall_bytes);
-    return n;
-  };
-  int64_t nitems = layout();
-  if (need > PRM_NOALLOC_SCRATCH_BYTES && P.tile != kNsTile) {
-    // smaller tiles have longer work lists; what fits on the largest one is taken
-    rc = make_plan(1, &rows, &cols, &c2, P, kNsTile);
-    if (rc) return rc;
-    nitems = layout();
-  }
-  if (need > PRM_NOALLOC_SCRATCH_BYTES)
+  if (L.priced > PRM_NOALLOC_SCRATCH_BYTES)
     return fail(PRM_ENOMEM, "a %s step of a %lld x %lld matrix needs %llu scratch bytes; the allocation-free step has %llu",
-                rho ? "refresh" : "row-wise", (long long)rows, (long long)cols, (unsigned long long)need,
+                rho ? "refresh" : "row-wise", (long long)rows, (long long)cols, (unsigned long long)L.priced,
                 (unsigned long long)PRM_NOALLOC_SCRATCH_BYTES);
+  if (L.end > sizeof(scratch)) return fail(PRM_EHIP, "internal: %llu scratch bytes laid out", (unsigned long long)L.end);
   build_lists(P, false);
   if (P.ints.size() > 64) return fail(PRM_EHIP, "internal: %zu int list entries", P.ints.size());
   for (int32_t v : P.ints)
@@ -1540,22 +1570,22 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   if (rho) {
     Chunk& ch = P.chunks[0];
     NsGroup& G = P.chain[0] ? ch.chain : ch.plain;  // the other group is empty
-    ok = ch.n_prologue == pm * pn && G.n_upper == T * (T + 1) / 2 && G.n_apply == tc * T &&
-         add(ch.off_prologue, ch.n_prologue, pn, 0) && add(G.off_upper, G.n_upper, T, 1) &&
-         add(G.off_apply, G.n_apply, T, 0);
+    ok = ch.n_prologue == L.pm * L.pn && G.n_upper == L.T * (L.T + 1) / 2 && G.n_apply == L.tc * L.T &&
+         add(ch.off_prologue, ch.n_prologue, L.pn, 0) && add(G.off_upper, G.n_upper, L.T, 1) &&
+         add(G.off_apply, G.n_apply, L.T, 0);
     G.off_gram = G.off_upper;  // one matrix: one order of its tiles serves both
   } else if (P.tall[0]) {
     const int32_t nt = P.n_tall4 + P.n_tall1;
-    ok = nt == P.nrb[0] * slabs && P.n_fin == fins && add(P.n_tall4 ? P.off_tall4 : P.off_tall1, nt, slabs, 0) &&
-         add(P.off_fin, fins, fins, 0);
+    ok = nt == P.nrb[0] * L.slabs && P.n_fin == L.fins && add(P.n_tall4 ? P.off_tall4 : P.off_tall1, nt, L.slabs, 0) &&
+         add(P.off_fin, L.fins, L.fins, 0);
   }
-  if (!ok || pos != nitems) return fail(PRM_EHIP, "internal: work list sizes disagree with the plan");
+  if (!ok || pos != L.nitems) return fail(PRM_EHIP, "internal: work list sizes disagree with the plan");
   s.nints = (int32_t)P.ints.size();
   char* base = nullptr;
   rc = noalloc_scratch(dev, &base);
   if (rc) return rc;
   std::vector<MatDesc> desc;
-  fill_descs(P, base + off_big, base + off_small, base + off_big, desc);
+  fill_descs(P, base + L.off_big, base + L.off_small, base + L.off_big, desc);
   s.d = desc[0];
   s.d.W = param;
   s.d.G = grad;
@@ -1567,8 +1597,8 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   c.stream = (hipStream_t)hip_stream;
   c.device = dev;
   c.d_desc = reinterpret_cast<MatDesc*>(base);
-  c.d_ints = reinterpret_cast<int32_t*>(base + off_ints);
-  c.d_items = reinterpret_cast<Item*>(base + off_items);
+  c.d_ints = reinterpret_cast<int32_t*>(base + L.off_ints);
+  c.d_items = reinterpret_cast<Item*>(base + L.off_items);
   const int64_t threads = std::max<int64_t>({(int64_t)pos, (int64_t)s.nints, 1});
   noalloc_setup_kernel<<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, c.stream>>>(s, c.d_desc, c.d_ints,
                                                                                            c.d_items);
@@ -1578,5 +1608,24 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
 }
 
 const char* prm_last_error(void) { return g_err.c_str(); }
+
+// Access for the tests, not part of the C ABI (no declaration in prm.h).
+//
+// What the allocation-free step of this shape would do, without a device: 1 if its
+// scratch fits the limit, 0 if it is refused; out: tile edge, bytes held against
+// the limit, bytes laid out, bytes of the array.
+int prm_internal_noalloc_plan(const prm_config* cfg, int64_t rows, int64_t cols, int64_t step, uint64_t out[4]) {
+  prm_config c2 = *cfg;
+  c2.workspace_budget_bytes = 1ull << 62;
+  Plan P;
+  NoallocLayout L;
+  const int rc = noalloc_plan(&c2, rows, cols, step, P, L);
+  if (rc) return rc;
+  out[0] = (uint64_t)P.tile;
+  out[1] = L.priced;
+  out[2] = L.end;
+  out[3] = sizeof(scratch);
+  return L.priced <= PRM_NOALLOC_SCRATCH_BYTES;
+}
 
 }  // extern "C"
