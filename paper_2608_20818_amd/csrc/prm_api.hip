@@ -277,9 +277,8 @@ void choose_tile(Plan& P) {
   }
 }
 
-// `tile`: the tile edge to plan for, 0 for choose_tile's.
 int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const prm_config* cfg,
-              Plan& P, int tile = 0) {
+              Plan& P) {
   int rc = validate_cfg(cfg);
   if (rc) return rc;
   if (n_mats < 0) return fail(PRM_EINVAL, "n_mats must be >= 0");
@@ -301,8 +300,7 @@ int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const pr
     P.chain.push_back(!cfg->ns_plain && !cfg->ns_precise && c >= 2 * r ? 1 : 0);
     P.s.push_back(shape_scale(m, n, cfg->scale_mode));
   }
-  if (tile) P.tile = tile;
-  else choose_tile(P);
+  choose_tile(P);
   for (int i = 0; i < n_mats; ++i) {
     P.rp.push_back(round_up(std::min(P.m[i], P.nn[i]), P.tile));
     P.cp.push_back(round_up(std::max(P.m[i], P.nn[i]), P.tile));
@@ -1040,8 +1038,18 @@ struct NoallocLayout {
     pm = (P.tall[0] ? P.cp[0] : P.rp[0]) / kPrologueTile;
     slabs = (P.nn[0] + 255) / 256;
     fins = (P.nn[0] + kFinCols - 1) / kFinCols;
+    auto refresh_items = [&](int64_t r, int64_t c, int64_t tile) {
+      return (r / kPrologueTile) * (c / kPrologueTile) + (r / tile) * (r / tile + 1) / 2 + (c / tile) * (r / tile);
+    };
     const int64_t tiles = (int64_t)P.nrb[0] * slabs;
-    nitems = rho ? pm * pn + T * (T + 1) / 2 + tc * T : (P.tall[0] ? tiles + fins : 0);
+    int64_t nprice;
+    if (rho) {
+      nitems = refresh_items(P.rp[0], P.cp[0], P.tile);
+      nprice = std::min(nitems, refresh_items(round_up(P.rp[0], kNsTile), round_up(P.cp[0], kNsTile), kNsTile));
+    } else {
+      nitems = P.tall[0] ? tiles + fins : 0;
+      nprice = P.tall[0] ? tiles + slabs : 0;
+    }
     off_ints = align256(sizeof(MatDesc));
     off_items = off_ints + 256;
     const uint64_t big = rho ? P.chunk_bytes : P.tall_bytes;
@@ -1051,7 +1059,7 @@ struct NoallocLayout {
     off_small = behind_items(nitems);
     off_big = off_small + align256(P.small_bytes);
     end = off_big + big;
-    priced = behind_items(rho ? nitems : (P.tall[0] ? tiles + slabs : 0)) + align256(P.small_bytes) + big;
+    priced = behind_items(nprice) + align256(P.small_bytes) + big;
   }
 };
 
@@ -1077,17 +1085,9 @@ int noalloc_scratch(int dev, char** out) {
 
 // Plan and layout of step `step` of one matrix.
 int noalloc_plan(const prm_config* cfg, int64_t rows, int64_t cols, int64_t step, Plan& P, NoallocLayout& L) {
-  int rc = make_plan(1, &rows, &cols, cfg, P);
-  if (rc) return rc;
-  const int rho = refresh_of(*cfg, step);
-  L = NoallocLayout(P, rho);
-  if (L.priced > PRM_NOALLOC_SCRATCH_BYTES && P.tile != kNsTile) {
-    // smaller tiles have longer work lists; what fits on the largest one is taken
-    rc = make_plan(1, &rows, &cols, cfg, P, kNsTile);
-    if (rc) return rc;
-    L = NoallocLayout(P, rho);
-  }
-  return PRM_OK;
+  const int rc = make_plan(1, &rows, &cols, cfg, P);  // prm_init's, so the same bits
+  if (rc == PRM_OK) L = NoallocLayout(P, refresh_of(*cfg, step));
+  return rc;
 }
 
 // One work list of the single matrix: `count` items from position `off`,
