@@ -196,18 +196,22 @@ __global__ __launch_bounds__(256) void ns_prologue_kernel(const MatDesc* __restr
 __global__ __launch_bounds__(256) void ns_alpha_kernel(const MatDesc* __restrict__ md,
                                                        const int32_t* __restrict__ mats,
                                                        NsParams p) {
-  constexpr int B = 32;
   __shared__ float red[4];
   const MatDesc& d = md[mats[blockIdx.x]];
   const int nt = d.ptiles_m * d.ptiles_n;
   float s = 0.f;
-  for (int i = threadIdx.x; i < nt; i += B * 256) {
-    float v[B];
+  auto sum = [&](auto batch) __attribute__((always_inline)) {
+    constexpr int B = decltype(batch)::value;
+    for (int i = threadIdx.x; i < nt; i += B * 256) {
+      float v[B];
 #pragma unroll
-    for (int k = 0; k < B; ++k) v[k] = i + 256 * k < nt ? Vec<float>::load1(d.partial + i + 256 * k) : 0.f;
+      for (int k = 0; k < B; ++k) v[k] = i + 256 * k < nt ? Vec<float>::load1(d.partial + i + 256 * k) : 0.f;
 #pragma unroll
-    for (int k = 0; k < B; ++k) s += v[k];
-  }
+      for (int k = 0; k < B; ++k) s += v[k];
+    }
+  };
+  if (nt <= 4 * 256) sum(std::integral_constant<int, 4>{});  // a small matrix does not step through 32
+  else sum(std::integral_constant<int, 32>{});
   s = block_sum<256>(s, red);
   if (threadIdx.x == 0) *d.alpha = 1.0f / (sqrtf(s) + p.eps_ns);
 }

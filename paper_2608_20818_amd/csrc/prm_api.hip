@@ -13,7 +13,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
+#include <iterator>
 #include <mutex>
+#include <queue>
 #include <string>
 #include <vector>
 
@@ -229,13 +232,23 @@ void wide_class(int64_t n, int& tpr, int& nch) {
 // its columns' partials itself.
 constexpr int kOwnNormBlocks = 64;
 
+// What a tile of the NS5 products costs by itself: its K / 64 stages plus a fixed
+// part, in us as measured (a stage of 64 moves 16, 32 or 64 KB into LDS, at 31 to 39
+// bytes per clock and CU); and how many an XCD runs at once (32 CUs, LDS for three 64
+// tiles on each).
+struct TilePrice {
+  int tile;
+  double stage, fixed;
+  int per_xcd;
+  double us(double k) const { return k / 64 * stage + fixed; }
+};
+constexpr TilePrice kTilePrice[3] = {{256, 1.17, 9.0, 32}, {128, 0.42, 5.0, 32}, {64, 0.16, 3.5, 96}};
+
 // Tile edge of the plan's NS5 products: 256 runs its MFMAs best, smaller tiles
 // spread a small set over more CUs and pad less.  A launch over the chip's 256 CUs
 // is priced as all its tiles' time over 256 plus half the longest tile (the uneven
 // end), but no less than the longest.  At 256 the plain and the factored group have
 // launches of their own; on small tiles they are priced as sharing every one.
-// A tile costs its K / 64 stages plus a fixed part, in us as measured (a stage
-// of 64 moves 16, 32 or 64 KB into LDS, at 31 to 39 bytes per clock and CU).
 // Measured refresh, us at 64 / 128 / 256, the choice first: six matrices with
 // r <= 256: 100 / 153 / 580; ten with r = 384 (three steps): 294 / 322 / 980;
 // seven with r <= 1001: 128: 550, 559 / 1500; five with r = 1024, precise: 128:
@@ -243,11 +256,9 @@ constexpr int kOwnNormBlocks = 64;
 // 256: 5700, 8831 / 6695; 25 with r = 768: 128: 1103, 1105 / 1471; 25 with r = 1600:
 // 256: 6269, though 128 took 5956.
 void choose_tile(Plan& P) {
-  struct Price { int tile; double stage, fixed; };
-  constexpr Price price[3] = {{256, 1.17, 9.0}, {128, 0.42, 5.0}, {64, 0.16, 3.5}};
   constexpr double kCus = 256;
   double best = 0;
-  for (const Price& pr : price) {
+  for (const TilePrice& pr : kTilePrice) {
     // Gram, r x r products, apply: time of all tiles, of the longest, launches
     // over the set (mean; the factored form runs 2, 14, 2, the plain one 5 each)
     struct Cost { double total[3], longest[3], count[3]; int mats; } cost[2] = {};
@@ -255,8 +266,7 @@ void choose_tile(Plan& P) {
       const double r = (double)round_up(std::min(P.m[i], P.nn[i]), pr.tile);
       const double c = (double)round_up(std::max(P.m[i], P.nn[i]), pr.tile);
       const double tr = r / pr.tile, tc = c / pr.tile;
-      const double time[3] = {c / 64 * (P.precise ? (pr.tile == 256 ? 3 : 2) : 1) * pr.stage + pr.fixed, r / 64 * pr.stage + pr.fixed,
-                              r / 64 * (P.precise ? 2 : 1) * pr.stage + pr.fixed};
+      const double time[3] = {pr.us(c * (P.precise ? (pr.tile == 256 ? 3 : 2) : 1)), pr.us(r), pr.us(r * (P.precise ? 2 : 1))};
       const double tiles[3] = {tr * (tr + 1) / 2, tr * (tr + 1) / 2, tr * tc};
       Cost& g = cost[pr.tile == kNsTile && P.chain[i]];
       ++g.mats;
@@ -358,9 +368,9 @@ int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const pr
 // Work groups are dispatched round-robin over the eight XCDs (group b runs on
 // XCD b mod 8), and each XCD has its own L2.  A GEMM work list orders the tiles
 // of a matrix in super-rows of kSuperRows tile rows, so that the groups an XCD
-// runs at once share a few row and column panels of the operands, deals whole
-// pieces of that order to the XCDs (XcdLists), and interleaves the XCDs' lists
-// into one launch order.
+// runs at once share a few row and column panels of the operands, deals pieces of
+// that order to the XCDs (XcdLists), and interleaves the XCDs' lists into one
+// launch order.
 constexpr int kXcds = 8;
 constexpr int kSuperRows = 4;
 
@@ -375,37 +385,73 @@ void tile_order(int32_t mat, int32_t tr, int32_t tc, bool upper, std::vector<Ite
   }
 }
 
-// Tiles of several matrices dealt to the XCDs.  Each matrix's tile order is cut
-// into `pieces` runs; a run goes to the XCD with the least work so far (a tile's
-// work is its K).  If whole matrices (or the given runs) leave the fullest XCD
-// more than 3% above the mean, the runs are halved: a set of 12 equal matrices
-// would give four XCDs twice the tiles of the others.  The launch order puts
-// XCD x's list on positions = x mod 8, with fillers (mat = -1) where it is
-// shorter than the others.
+// The launch order of the tiles of several matrices (add: a matrix's tile order and
+// the K of its tiles), in one of two ways.
+//
+// In turn: matrix i, or eighth x of every matrix (in_turn(8)), is XCD i mod 8's (x's)
+// list, and the lists are interleaved as long as they last: the tiles of those that
+// are longer then spread over all XCDs.
+//
+// Balanced: every matrix's order is cut into runs, and a run goes to the XCD with the
+// least work so far (a tile's work is its K).  If whole matrices leave the fullest
+// XCD more than 3% above the mean, the runs are halved, down to single tiles.  XCD
+// x's list is on positions = x mod 8, with fillers (mat = -1) where it is shorter
+// than the others.
+//
+// On 256 tiles balanced lists pay where matrices differ in K or where the tiles of the
+// longer lists would all run at the end; where they save no time by the count, the
+// tiles of a matrix that they scatter over the XCDs share less in the L2s.  Measured,
+// us in turn / balanced, 256 tiles: Gram of the weights of three blocks of width 2048 1422 / 1199,
+// two of 3072 3006 / 2219, one of 4096 3672 / 2587, three of 1408 650 / 664; the r x r
+// products (one r) of three blocks of width 1280 895 / 948, 1408 1076 / 1184, 1536
+// 1096 / 1201, of ten matrices of eight shapes 2126 / 1841; apply within 1% of each
+// other, or 679 / 703, 1641 / 1691.  The lists of smaller tiles are always balanced: a
+// few matrices' tiles lie scattered in turn (refresh of one 2048 x 6144 513 / 500, of
+// five matrices of five shapes 2004 / 1909).
 struct XcdLists {
-  std::vector<std::vector<Item>> mats;
-  std::vector<double> weight;
-  int pieces;
-  explicit XcdLists(int first_pieces) : pieces(first_pieces) {}
-  void add(const std::vector<Item>& tiles, double k) {
-    mats.push_back(tiles);
-    weight.push_back(k);
+  struct Tiles {
+    std::vector<Item> items;
+    double k;
+  };
+  std::vector<Tiles> mats;
+  const TilePrice& price;
+  explicit XcdLists(const TilePrice& p) : price(p) {}
+  void add(const std::vector<Item>& tiles, double k) { mats.push_back(Tiles{tiles, k}); }
+
+  std::vector<Item> in_turn(int pieces = 1) const {
+    std::vector<std::vector<Item>> per(kXcds);
+    size_t total = 0;
+    for (size_t i = 0; i < mats.size(); ++i) {
+      const auto& t = mats[i].items;
+      total += t.size();
+      for (int x = 0; x < pieces; ++x) {
+        auto& to = per[pieces == 1 ? i % kXcds : x];
+        to.insert(to.end(), t.begin() + t.size() * x / pieces, t.begin() + t.size() * (x + 1) / pieces);
+      }
+    }
+    std::vector<Item> out;
+    out.reserve(total);
+    for (size_t k = 0; out.size() < total; ++k)
+      for (const auto& v : per)
+        if (k < v.size()) out.push_back(v[k]);
+    return out;
   }
-  std::vector<Item> interleaved() const {
+
+  std::vector<Item> balanced(size_t pieces = 1) const {
     size_t most = 0;
-    for (const auto& t : mats) most = std::max(most, t.size());
+    for (const auto& t : mats) most = std::max(most, t.items.size());
     std::vector<std::vector<Item>> per;
     for (size_t d = pieces;; d *= 2) {
       per.assign(kXcds, {});
       std::vector<double> load(kXcds, 0.0);
-      for (size_t i = 0; i < mats.size(); ++i) {
-        const size_t n = mats[i].size();
+      for (const auto& t : mats) {
+        const size_t n = t.items.size();
         for (size_t k = 0; k < d; ++k) {
           const size_t lo = n * k / d, hi = n * (k + 1) / d;
           if (lo == hi) continue;
           const size_t x = std::min_element(load.begin(), load.end()) - load.begin();
-          per[x].insert(per[x].end(), mats[i].begin() + lo, mats[i].begin() + hi);
-          load[x] += weight[i] * (double)(hi - lo);
+          per[x].insert(per[x].end(), t.items.begin() + lo, t.items.begin() + hi);
+          load[x] += t.k * (double)(hi - lo);
         }
       }
       double sum = 0, top = 0;
@@ -421,6 +467,34 @@ struct XcdLists {
     for (int x = 0; x < kXcds; ++x)
       for (size_t k = 0; k < per[x].size(); ++k) out[k * kXcds + x] = per[x][k];
     return out;
+  }
+
+  // When the last tile of such a list ends: each XCD starts its tiles in order as
+  // its slots come free.
+  double time(const std::vector<Item>& list) const {
+    std::vector<std::pair<int32_t, double>> us;
+    for (const auto& t : mats) us.push_back({t.items.empty() ? -1 : t.items[0].mat, price.us(t.k)});
+    std::sort(us.begin(), us.end());
+    double end = 0;
+    for (int x = 0; x < kXcds; ++x) {
+      std::priority_queue<double, std::vector<double>, std::greater<double>> free;
+      for (int i = 0; i < price.per_xcd; ++i) free.push(0.0);
+      for (size_t b = x; b < list.size(); b += kXcds) {
+        if (list[b].mat < 0) continue;
+        const double t = free.top() + std::lower_bound(us.begin(), us.end(), std::make_pair(list[b].mat, 0.0))->second;
+        free.pop();
+        free.push(t);
+        end = std::max(end, t);
+      }
+    }
+    return end;
+  }
+
+  // The preferred list, unless the other one ends 3% earlier.
+  std::vector<Item> choose(bool prefer_balanced) const {
+    std::vector<Item> a = in_turn(), b = balanced();
+    const double ta = time(a), tb = time(b);
+    return (prefer_balanced ? ta >= 0.97 * tb : tb < 0.97 * ta) ? b : a;
   }
 };
 
@@ -496,12 +570,14 @@ void build_lists(Plan& P, bool items) {
     }
     for (int grp = 0; grp < 2; ++grp) {
       NsGroup& G = grp ? ch.chain : ch.plain;
-      // symmetric products: whole matrices per XCD where that balances (their
-      // tiles share the r x r panels in the XCD's L2); the Gram's K is c, that of
-      // the others r, so each has its own balance.  Apply: an eighth of each
-      // matrix per XCD, so all XCDs stream the same factor at the same time (it
-      // is read by every tile row; the last-level cache serves the repeats).
-      XcdLists g(1), u(1), a(kXcds);
+      // symmetric products: matrices per XCD (their tiles share the r x r panels
+      // in the XCD's L2); the Gram's K is c, that of the others r, so each has its
+      // own list.  Apply: an eighth of each matrix per XCD, so all XCDs stream the
+      // same factor at the same time (it is read by every tile row; the last-level
+      // cache serves the repeats).
+      const TilePrice& price = *std::find_if(std::begin(kTilePrice), std::end(kTilePrice),
+                                             [&](const TilePrice& t) { return t.tile == P.tile; });
+      XcdLists g(price), u(price), a(price);
       std::vector<Item> tiles;
       for (int i : ch.mats) {
         if (P.chain[i] != grp) continue;
@@ -534,9 +610,10 @@ void build_lists(Plan& P, bool items) {
         a.add(tiles, rp);
       }
       if (!items) continue;
-      G.gram = g.interleaved();
-      G.upper = u.interleaved();
-      G.apply = a.interleaved();
+      const bool large = P.tile == kNsTile;
+      G.gram = large ? g.choose(true) : g.balanced();
+      G.upper = large ? u.choose(false) : u.balanced();
+      G.apply = large ? a.in_turn(kXcds) : a.balanced(kXcds);
       G.n_gram = (int32_t)G.gram.size();
       G.n_upper = (int32_t)G.upper.size();
       G.n_apply = (int32_t)G.apply.size();
@@ -1626,6 +1703,25 @@ int prm_internal_noalloc_plan(const prm_config* cfg, int64_t rows, int64_t cols,
   out[2] = L.end;
   out[3] = sizeof(scratch);
   return L.priced <= PRM_NOALLOC_SCRATCH_BYTES;
+}
+
+// A work list of the plan's first chunk, without a device: kind as GemmKind (Gram, the
+// r x r products or apply) of the plain or the factored group; out: cap pairs of
+// matrix (-1: filler) and tile tm << 16 | tn.  Returns the list's length.
+int prm_internal_work_list(int32_t n, const int64_t* rows, const int64_t* cols, const prm_config* cfg, int32_t factored,
+                           int32_t kind, int32_t* out, int32_t cap) {
+  Plan P;
+  const int rc = make_plan(n, rows, cols, cfg, P);
+  if (rc) return rc;
+  build_lists(P, true);
+  if (P.chunks.empty()) return 0;
+  const NsGroup& G = factored ? P.chunks[0].chain : P.chunks[0].plain;
+  const std::vector<Item>& list = kind == GEMM_GRAM ? G.gram : kind == GEMM_APPLY ? G.apply : G.upper;
+  for (size_t i = 0; i < list.size() && (int32_t)i < cap; ++i) {
+    out[2 * i] = list[i].mat;
+    out[2 * i + 1] = list[i].tm << 16 | list[i].tn;
+  }
+  return (int)list.size();
 }
 
 }  // extern "C"
