@@ -114,6 +114,7 @@ template <> struct VecNT<float> {
     store4(p + 4, v + 4);
   }
   __device__ __forceinline__ static float load1(const float* p) { return __builtin_nontemporal_load(gptr(p)); }
+  __device__ __forceinline__ static float raw1(const float* p) { return load1(p); }
   __device__ __forceinline__ static void store1(float* p, float v) { __builtin_nontemporal_store(v, gptr(p)); }
 };
 
@@ -140,13 +141,16 @@ template <> struct VecNT<uint16_t> {
                        pack_bf2(v[6], v[7])};
     __builtin_nontemporal_store(x, gptr(reinterpret_cast<u32x4_t*>(p)));
   }
-  __device__ __forceinline__ static float load1(const uint16_t* p) {
-    return bf2f(__builtin_nontemporal_load(gptr(p)));
-  }
+  __device__ __forceinline__ static float load1(const uint16_t* p) { return bf2f(raw1(p)); }
+  // an element as stored, for to_float once a batch of loads has been issued
+  __device__ __forceinline__ static uint16_t raw1(const uint16_t* p) { return __builtin_nontemporal_load(gptr(p)); }
   __device__ __forceinline__ static void store1(uint16_t* p, float v) {
     __builtin_nontemporal_store((uint16_t)f2bf(v), gptr(p));
   }
 };
+
+__device__ __forceinline__ float to_float(float v) { return v; }
+__device__ __forceinline__ float to_float(uint16_t v) { return bf2f(v); }
 
 // ---- the same for rows that start on any element -----------------------------
 // Eight consecutive elements with only element alignment: the hardware takes

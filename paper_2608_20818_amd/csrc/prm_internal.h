@@ -107,12 +107,13 @@ hipError_t launch_rw_first(DType wt, DType gt, const MatDesc* md, const Item* it
                            const RwParams& p, hipStream_t s);
 // Tall matrices: column statistics, column norms, parameter write (own_norms:
 // the last sums the statistics itself).  aligned: every width of the launch is
-// a multiple of 4.
+// a multiple of 4; one_row (other widths, without own_norms): the parameter write
+// loads row by row.
 hipError_t launch_rw_tall_stats(bool aligned, DType gt, const MatDesc* md, const Item* items,
                                 int32_t nitems, const RwParams& p, hipStream_t s);
 hipError_t launch_rw_tall_finalize(const MatDesc* md, const Item* items, int32_t nitems,
                                    const RwParams& p, hipStream_t s);
-hipError_t launch_rw_tall_apply(bool aligned, bool own_norms, DType wt, DType gt, const MatDesc* md,
+hipError_t launch_rw_tall_apply(bool aligned, bool own_norms, bool one_row, DType wt, DType gt, const MatDesc* md,
                                 const Item* items, int32_t nitems, const RwParams& p,
                                 hipStream_t s);
 

@@ -377,10 +377,14 @@ __device__ __forceinline__ void tall_stats(const MatDesc& d, const Item& it, flo
 }
 
 // n % 4 != 0: one column per thread, 256 columns and kTallRows rows per block,
-// the loads of kBatch rows issued together.  (16-byte accesses at any address,
-// as the ragged rows use, ran at half the rate here: 8001 x 3003, 154 us against
-// 64, where a wave's 1 KB span starts and ends inside a line at every row.)
-constexpr int kBatch = 8;
+// the loads of kBatch rows issued together: without a branch (rows past the last
+// read the last again) and as stored (a 16-bit value converted under a branch is
+// waited for there, row by row).  Whole step of bf16 weights and gradients, us, row by
+// row / 8 / 16 rows: 4001 x 1003 42.6 / 25.1 / 22.2, 8001 x 3003 119 / 97 / 94.
+// (16-byte accesses at any address, as the ragged rows use, ran at half the rate here:
+// 8001 x 3003, 154 us against 64, where a wave's 1 KB span starts and ends inside a
+// line at every row.)
+constexpr int kBatch = 16;
 static_assert(kTallRows % kBatch == 0, "whole batches");
 
 template <DType GD>
@@ -395,19 +399,20 @@ __device__ __forceinline__ void tall_stats_scalar(const MatDesc& d, const Item& 
   float* M = d.M + r0 * n + col;
   float acc = 0.f;
   for (int b = 0; b < rows; b += kBatch) {
-    float g[kBatch], m[kBatch];
+    GT g[kBatch];
+    float m[kBatch];
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      const uint32_t off = (uint32_t)min(b + q, rows - 1) * (uint32_t)n;  // < 32 * 2^24
+      g[q] = VecNT<GT>::raw1(G + off);
+      m[q] = Vec<float>::load1(M + off);
+    }
 #pragma unroll
     for (int q = 0; q < kBatch; ++q)
       if (b + q < rows) {
-        g[q] = VecNT<GT>::load1(G + (b + q) * n);
-        m[q] = Vec<float>::load1(M + (b + q) * n);
-      }
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q)
-      if (b + q < rows) {
-        const float v = new_momentum<GD, false>(m[q], g[q], p);
-        Vec<float>::store1(M + (b + q) * n, v);
-        const float u = p.nesterov ? fmaf(p.beta, v, g[q]) : v;
+        const float gq = to_float(g[q]), v = new_momentum<GD, false>(m[q], gq, p);
+        Vec<float>::store1(M + (uint32_t)(b + q) * (uint32_t)n, v);
+        const float u = p.nesterov ? fmaf(p.beta, v, gq) : v;
         acc = fmaf(u, u, acc);
       }
   }
@@ -515,9 +520,9 @@ __global__ __launch_bounds__(256) void rw_tall_finalize_kernel(const MatDesc* __
 
 // Tall pass 2: D = gamma * s * U / nu_col and the parameter write, on the same
 // one-shot tiles as pass 1 (ALIGNED: n % 4 == 0; otherwise one column per
-// thread).  OWN_NORMS: the block sums its 256 columns' partials itself instead
+// thread, the loads of BATCH rows issued together).  OWN_NORMS: the block sums its 256 columns' partials itself instead
 // of reading what the finalize launch left (short matrices).
-template <DType WD, DType GD, bool NEST, bool ALIGNED, bool OWN_NORMS>
+template <DType WD, DType GD, bool NEST, bool ALIGNED, bool OWN_NORMS, int BATCH>
 __global__ __launch_bounds__(256) void rw_tall_apply_kernel(const MatDesc* __restrict__ md,
                                                             const Item* __restrict__ items,
                                                             RwParams p) {
@@ -584,24 +589,27 @@ __global__ __launch_bounds__(256) void rw_tall_apply_kernel(const MatDesc* __res
     WT* W = reinterpret_cast<WT*>(d.W) + base;
     float* const D = (p.write_d && d.D) ? d.D + base : nullptr;
     float kc = 0.f;
-    for (int b = 0; b < rows; b += kBatch) {
-      float m[kBatch], wv[kBatch], g[NEST ? kBatch : 1];
+    for (int b = 0; b < rows; b += BATCH) {
+      float m[BATCH];
+      WT wv[BATCH];
+      GT g[NEST ? BATCH : 1];
 #pragma unroll
-      for (int q = 0; q < kBatch; ++q)
-        if (b + q < rows) {
-          m[q] = Vec<float>::load1(M + (b + q) * n);
-          wv[q] = VecNT<WT>::load1(W + (b + q) * n);
-          if constexpr (NEST) g[q] = VecNT<GT>::load1(G + (b + q) * n);
-        }
+      for (int q = 0; q < BATCH; ++q) {
+        const uint32_t off = (uint32_t)min(b + q, rows - 1) * (uint32_t)n;  // < 32 * 2^24
+        m[q] = Vec<float>::load1(M + off);
+        wv[q] = VecNT<WT>::raw1(W + off);
+        if constexpr (NEST) g[q] = VecNT<GT>::raw1(G + off);
+      }
       if (b == 0) kc = gs * (OWN_NORMS ? col_inverse(d, own, p.eps) : Vec<float>::load1(d.colinv + own));
 #pragma unroll
-      for (int q = 0; q < kBatch; ++q)
+      for (int q = 0; q < BATCH; ++q)
         if (b + q < rows) {
           float u = m[q];
-          if constexpr (NEST) u = fmaf(p.beta, m[q], g[q]);
+          if constexpr (NEST) u = fmaf(p.beta, m[q], to_float(g[q]));
           const float dv = u * kc;
-          VecNT<WT>::store1(W + (b + q) * n, new_weight<WD, false>(wv[q], dv, p));
-          if (D) Vec<float>::store1(D + (b + q) * n, dv);
+          const uint32_t off = (uint32_t)(b + q) * (uint32_t)n;
+          VecNT<WT>::store1(W + off, new_weight<WD, false>(to_float(wv[q]), dv, p));
+          if (D) Vec<float>::store1(D + off, dv);
         }
     }
   }
@@ -741,18 +749,26 @@ hipError_t launch_rw_tall_finalize(const MatDesc* md, const Item* items, int32_t
   return hipGetLastError();
 }
 
-hipError_t launch_rw_tall_apply(bool aligned, bool own_norms, DType wt, DType gt, const MatDesc* md,
+hipError_t launch_rw_tall_apply(bool aligned, bool own_norms, bool one_row, DType wt, DType gt, const MatDesc* md,
                                 const Item* items, int32_t nitems, const RwParams& p,
                                 hipStream_t s) {
   if (nitems <= 0) return hipSuccess;
   return by_types(wt, gt, [&](auto w, auto g) {
     constexpr DType W = decltype(w)::value, G = decltype(g)::value;
-    auto run = [&](auto nest, auto al, auto own) {
-      rw_tall_apply_kernel<W, G, decltype(nest)::value, decltype(al)::value, decltype(own)::value>
+    auto run = [&](auto nest, auto al, auto own, auto batch) {
+      rw_tall_apply_kernel<W, G, decltype(nest)::value, decltype(al)::value, decltype(own)::value, decltype(batch)::value>
           <<<dim3(nitems), dim3(256), 0, s>>>(md, items, p);
     };
-    auto own = [&](auto nest, auto al) { own_norms ? run(nest, al, std::true_type{}) : run(nest, al, std::false_type{}); };
-    auto al = [&](auto nest) { aligned ? own(nest, std::true_type{}) : own(nest, std::false_type{}); };
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, kBatch> many{};
+    auto own = [&](auto nest, auto al, auto batch) {
+      own_norms ? run(nest, al, std::true_type{}, batch) : run(nest, al, std::false_type{}, batch);
+    };
+    auto al = [&](auto nest) {
+      if (aligned) own(nest, std::true_type{}, many);
+      else if (one_row) run(nest, std::false_type{}, std::false_type{}, one);
+      else own(nest, std::false_type{}, many);
+    };
     p.nesterov ? al(std::true_type{}) : al(std::false_type{});
     return hipGetLastError();
   });

@@ -61,3 +61,29 @@ def test_row_lengths_against_the_oracle(name, wdt, gdt, nesterov):
         else:  # decay W0 - lr D in fp32: two roundings of each term
             assert pc.rel(pc.to_host(W[k]), Wo) <= 2.0 ** -22, shapes[k]
         assert torch.equal(W[k], W2[k]) and torch.equal(M[k], M2[k]), shapes[k]
+
+
+@pytest.mark.parametrize("wdt,gdt,nesterov", [(1, 0, 1), (0, 1, 0), (1, 1, 0), (0, 0, 1)])
+def test_bits_of_a_matrix_do_not_depend_on_its_set(wdt, gdt, nesterov):
+    """Matrices alone and beside so many elements that the launches are split and
+    loaded in other ways."""
+    few = [(2047, 1001), (65, 31), (700, 100), (9, 513), (64, 64)]
+    cfg = prm.config_default(K=2, lr=0.02, wd=0.1, param_dtype=wdt, grad_dtype=gdt, nesterov=nesterov)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+
+    def draw(shape, dtype, scale):
+        return torch.empty(shape, device="cuda").normal_(0, scale, generator=gen).to(pc.torch_dtype(dtype))
+
+    for more in ([(31000, 2001)], [(2047, 999)] * 12, [(40, 513)] * 300):
+        shapes = few + more
+        print(f"  W {wdt} G {gdt} nesterov {nesterov} beside {len(more)} of {more[0]}", flush=True)
+        W, G, M = ([draw(s, t, x) for s in shapes] for t, x in ((wdt, 0.02), (gdt, 0.01), (0, 0.02)))
+        W2, M2 = [w.clone() for w in W[:len(few)]], [m.clone() for m in M[:len(few)]]
+        with prm.Optimizer(shapes, cfg) as opt:
+            opt.step(W, G, M, 1)
+            torch.cuda.synchronize()
+        for i, s in enumerate(few):
+            with prm.Optimizer([s], cfg) as opt:
+                opt.step(W2[i:i + 1], G[i:i + 1], M2[i:i + 1], 1)
+                torch.cuda.synchronize()
+            assert torch.equal(W[i], W2[i]) and torch.equal(M[i], M2[i]), s
