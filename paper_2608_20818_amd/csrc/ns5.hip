@@ -127,30 +127,33 @@ __global__ __launch_bounds__(256) void ns_prologue_kernel(const MatDesc* __restr
     }
   } else {
     // rows that start anywhere: a lane per column, so that a wave's access is one
-    // span of a row, and the loads of eight rows together (four elements of a row
-    // per lane, one by one, took 109 us for 15 M elements)
-    const int c = threadIdx.x & 63, r4 = threadIdx.x >> 6;
+    // span of a row, and the loads of eight rows together, as stored and under one
+    // branch, where rows past the wave's last read that one again (four elements of a
+    // row per lane, one by one, took 109 us for 15 M elements)
+    const int c = threadIdx.x & 63, r4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t col = C0 + c;
+    const int nr = (int)max((int64_t)0, min((int64_t)T / 4, (m - R0 - r4 + 3) / 4));  // rows r4, r4 + 4, ...
+    const int64_t first = (R0 + r4) * n + col;
 #pragma unroll
     for (int b = 0; b < T / 4; b += 8) {
-      float g[8], mm[8];
+      GT g[8];
+      float mm[8];
+      if (b < nr && col < n) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int64_t row = R0 + r4 + 4 * (b + q);
-        if (row < m && col < n) {
-          g[q] = VecNT<GT>::load1(G + row * n + col);
-          mm[q] = Vec<float>::load1(M + row * n + col);
+        for (int q = 0; q < 8; ++q) {
+          const int64_t off = first + 4 * (int64_t)min(b + q, nr - 1) * n;
+          g[q] = VecNT<GT>::raw1(G + off);
+          mm[q] = Vec<float>::load1(M + off);
         }
       }
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const int r = r4 + 4 * (b + q);
-        const int64_t row = R0 + r;
         float u = 0.f;
-        if (row < m && col < n) {
-          const float v = p.beta * mm[q] + p.gcoef * g[q];
-          Vec<float>::store1(M + row * n + col, v);
-          u = p.nesterov ? g[q] + p.beta * v : v;
+        if (b + q < nr && col < n) {
+          const float gq = to_float(g[q]), v = p.beta * mm[q] + p.gcoef * gq;
+          Vec<float>::store1(M + first + 4 * (int64_t)(b + q) * n, v);
+          u = p.nesterov ? gq + p.beta * v : v;
         }
         ss += u * u;
         const uint32_t h = f2bf(u);

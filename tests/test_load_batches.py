@@ -55,3 +55,9 @@ def test_the_count():
                                     "rw_tall_apply_kernelILNS_5DTypeE0ELS1_1ELb1ELb0ELb0ELi16E"])
 def test_rows_of_odd_tall_matrices(assembly, kernel):
     assert in_flight(assembly("rowwise.hip"), kernel, "global_load_ushort") >= 24
+
+
+# <gradient, hi + lo>
+@pytest.mark.parametrize("kernel", ["ns_prologue_kernelILNS_5DTypeE1ELb0E", "ns_prologue_kernelILNS_5DTypeE1ELb1E"])
+def test_rows_of_the_refresh_prologue(assembly, kernel):
+    assert in_flight(assembly("ns5.hip"), kernel, "global_load_ushort") >= 12
