@@ -228,9 +228,15 @@ void wide_class(int64_t n, int& tpr, int& nch) {
   else if (chunks <= 512 * 8 && n % 8 == 0) { tpr = 512; nch = (int)((chunks + 511) / 512); }
 }
 
-// Tall matrices up to this many row blocks: every tile of the second pass sums
-// its columns' partials itself.
+// Every tile of the second tall pass sums its columns' partials itself up to this many
+// row blocks a matrix and this many partials' rows in all (row blocks times tiles; a row
+// is 1 KB): it saves the finalize launch, but the tiles read their partials at their
+// start, which a grid of many tiles does not hide.  Whole step with the finalize over
+// without, at 32 row blocks of 1000 columns and 16K / 64K / 188K rows: 1.12 / 1.02 /
+// 1.00; 64 of 1000: 1.08 (32K) / 1.04 (64K) / 0.98 (128K) / 0.97; 64 of 300: 1.02
+// (56K) / 1.00 (104K) / 0.90 (208K); 48 of 301: 0.98 (40K) / 0.96 (76K) / 0.92 (157K).
 constexpr int kOwnNormBlocks = 64;
+constexpr int64_t kOwnNormRows = 64 << 10;
 
 // What a tile of the NS5 products costs by itself: its K / 64 stages plus a fixed
 // part, in us as measured (a stage of 64 moves 16, 32 or 64 KB into LDS, at 31 to 39
@@ -503,8 +509,10 @@ struct XcdLists {
 void build_lists(Plan& P, bool items) {
   // row-wise wide classes
   int most_blocks = 0, firsts = 0;
+  int64_t norm_rows = 0;
   for (int i = 0; i < P.n; ++i) {
     most_blocks = std::max(most_blocks, P.nrb[i]);
+    norm_rows += (int64_t)P.nrb[i] * P.nrb[i] * ((P.nn[i] + 255) / 256);  // 0 row blocks unless tall
     if (P.tall[i]) continue;
     const int64_t n = P.nn[i];
     int tpr, nch;
@@ -533,7 +541,7 @@ void build_lists(Plan& P, bool items) {
     put(*wc, tpr == 64 ? 4 : 1);
     if (tpr == 64 || tpr == 256) put(P.first, tpr == 64 ? 4 : 1);
   }
-  P.own_norms = most_blocks <= kOwnNormBlocks;
+  P.own_norms = most_blocks <= kOwnNormBlocks && norm_rows <= kOwnNormRows;
   // tall lists
   for (int i = 0; i < P.n; ++i) {
     if (!P.tall[i]) continue;
@@ -1725,6 +1733,18 @@ int prm_internal_work_list(int32_t n, const int64_t* rows, const int64_t* cols, 
     out[2 * i + 1] = list[i].tm << 16 | list[i].tn;
   }
   return (int)list.size();
+}
+
+// How a row-wise step of the set is launched, without a device: out: the second tall
+// pass sums its own norms; one launch for every first pass.
+int prm_internal_rowwise_plan(int32_t n, const int64_t* rows, const int64_t* cols, const prm_config* cfg, int32_t out[2]) {
+  Plan P;
+  const int rc = make_plan(n, rows, cols, cfg, P);
+  if (rc) return rc;
+  build_lists(P, false);
+  out[0] = P.own_norms;
+  out[1] = P.rw_first;
+  return PRM_OK;
 }
 
 }  // extern "C"
