@@ -61,3 +61,9 @@ def test_rows_of_odd_tall_matrices(assembly, kernel):
 @pytest.mark.parametrize("kernel", ["ns_prologue_kernelILNS_5DTypeE1ELb0E", "ns_prologue_kernelILNS_5DTypeE1ELb1E"])
 def test_rows_of_the_refresh_prologue(assembly, kernel):
     assert in_flight(assembly("ns5.hip"), kernel, "global_load_ushort") >= 12
+
+
+# widths that are multiples of 4: fp32 with Nesterov, norms from the finalize
+def test_rows_of_aligned_tall_matrices_with_nesterov(assembly):
+    kernel = "rw_tall_apply_kernelILNS_5DTypeE0ELS1_0ELb1ELb1ELb0ELi16E"
+    assert in_flight(assembly("rowwise.hip"), kernel, "global_load_dwordx4") >= 20
