@@ -136,6 +136,7 @@ struct Plan {
   int32_t tile = kNsTile;           // tile edge of the NS5 products: 64, 128 (ns5_small.hip) or 256 (ns5.hip)
   std::vector<int32_t> chain;       // NS5 in the factored form (oriented c >= 2r)
   int32_t precise = 0;              // every iterate carried as hi + lo bf16 (plain path)
+  int32_t param_dtype = F32, grad_dtype = F32;
   std::vector<float> s;
   std::vector<uint64_t> ws_off;     // offset of the matrix's NS region inside the chunk area
   std::vector<uint64_t> small_off;  // partial sums + alpha
@@ -302,6 +303,8 @@ int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const pr
   P = Plan();
   P.n = n_mats;
   P.precise = cfg->ns_precise;
+  P.param_dtype = cfg->param_dtype;
+  P.grad_dtype = cfg->grad_dtype;
   for (int i = 0; i < n_mats; ++i) {
     const int64_t m = rows[i], n = cols[i];
     if (m < 1 || n < 1 || m > kMaxDim || n > kMaxDim)
@@ -504,11 +507,46 @@ struct XcdLists {
   }
 };
 
+// Whether one launch takes every first pass of a row-wise step (tall statistics, wide
+// rows up to 256 threads) instead of one per class.  It saves the launches' starts and
+// ends, kLaunchUs each; but all its blocks have the registers of the longest rows, so
+// that only two of them fit a CU, which is what blocks of short rows or narrow
+// tiles are bound by: kBlockUs a block, where their own kernels have up to eight in
+// flight.  Both ways are priced at the larger of that and their bytes.  Over 2124 random
+// sets of 2 to 150 matrices this picks the faster way or one within 2% in 92% of them,
+// within 5% in 97%; always one launch, as it was up to 4e8 elements, was more than 5%
+// slower in 17% of them, up to 1.9 times.  us apart / in one launch: two blocks of
+// width 384 35 / 26, six of 1024 326 / 303, three of 2048 605 / 596; 100 of 512 x 513
+// with 200 of 64 x 64 111 / 349.  Beyond 4e8 elements the registers cost more than
+// the ends: six blocks of 2048 1175 / 1194.
+bool one_first_launch(const Plan& P) {
+  constexpr double kBlockUs = 8, kLaunchUs = 13, kBytesPerUs = 5.8e6, kCus = 256;
+  constexpr double kAll = 4e8;
+  constexpr int per_cu[9] = {0, 8, 6, 4, 3, 3, 2, 2, 2};  // blocks in flight of a class, by chunks per thread
+  const double gb = P.grad_dtype == BF16 ? 2 : 4, wb = P.param_dtype == BF16 ? 2 : 4;
+  double elems = 0, bytes = 0, blocks = 0, apart = 0;
+  int classes = 0;
+  auto add = [&](double n, double b, int in_flight) {
+    if (n == 0) return;
+    ++classes;
+    blocks += n;
+    bytes += b;
+    apart += std::max(b / kBytesPerUs, n * kBlockUs / (kCus * in_flight)) + kLaunchUs;
+  };
+  add(P.n_tall4, P.tall_elems4 * (gb + 8), 5);
+  add(P.n_tall1, P.tall_elems1 * (gb + 8), 8);
+  for (const auto& w : P.wide)
+    if (w.tpr != 512) add(w.nblocks, w.elems * (gb + 8 + 2 * wb), per_cu[w.nch]);
+  for (int i = 0; i < P.n; ++i) elems += (double)P.m[i] * P.nn[i];
+  const double one = std::max(bytes / kBytesPerUs, blocks * kBlockUs / (kCus * 2)) + kLaunchUs;
+  return classes > 1 && elems <= kAll && one < apart;
+}
+
 // Work lists (host side).  `items` false (the allocation-free step, which writes
 // its one matrix's lists on the device): only their lengths.
 void build_lists(Plan& P, bool items) {
   // row-wise wide classes
-  int most_blocks = 0, firsts = 0;
+  int most_blocks = 0;
   int64_t norm_rows = 0;
   for (int i = 0; i < P.n; ++i) {
     most_blocks = std::max(most_blocks, P.nrb[i]);
@@ -557,15 +595,7 @@ void build_lists(Plan& P, bool items) {
       for (int32_t sb = 0; sb < slabs; ++sb) L.push_back(Item{i, rb, sb, 0});
     for (int32_t cb = 0; cb < fins; ++cb) P.fin_items.push_back(Item{i, 0, cb, 0});
   }
-  // one launch for all of them instead of one per class and pass, over the weights
-  // of one to three blocks of width 384 to 2560: 28 -> 18 us at 2.2 M elements,
-  // 117 -> 95 at 25 M, 617 -> 598 at 189 M, 1089 -> 1044 at 295 M; but 4000 ->
-  // 4083 at 1.26 G, where the ends of the launches weigh less than the registers
-  // of the longest rows
-  double elems = 0;
-  for (int i = 0; i < P.n; ++i) elems += (double)P.m[i] * P.nn[i];
-  for (const auto& w : P.wide) firsts += w.tpr != 512;
-  P.rw_first = elems <= 4e8 && firsts + (P.n_tall4 > 0) + (P.n_tall1 > 0) > 1;
+  P.rw_first = one_first_launch(P);
   // NS5 lists per chunk and group
   for (auto& ch : P.chunks) {
     for (int i : ch.mats) {

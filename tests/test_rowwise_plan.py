@@ -23,3 +23,18 @@ def plan(shapes, wdt=prm.BF16, gdt=prm.BF16):
     ([(1536, 384)] * 64, 0), ([(256, 256)], 1), ([(64, 128)] * 5, 1), ([], 1)])
 def test_own_norms(shapes, own):
     assert plan(shapes)[0] == own
+
+
+def dit(blocks, h):
+    return [(h, 3 * h), (h, h), (h, 4 * h), (4 * h, h), (h, 6 * h)] * blocks
+
+
+@pytest.mark.parametrize("shapes,first", [
+    # long rows, and few blocks: the launches' ends count
+    (dit(2, 384), 1), (dit(6, 1024), 1), (dit(3, 2048), 1), ([(9, 513), (513, 9), (64, 64)], 1),
+    # many short rows or narrow tiles: two blocks on a CU are too few
+    ([(64, 64)] * 200 + [(512, 513)] * 100, 0), ([(3000, 600), (64, 4000)] * 20 + [(500, 520)] * 60, 0),
+    # one class, none, and too large
+    ([(512, 513)] * 100, 0), ([], 0), (dit(6, 2048), 0)])
+def test_one_first_launch(shapes, first):
+    assert plan(shapes)[1] == first
