@@ -153,42 +153,40 @@ __device__ __forceinline__ float to_float(float v) { return v; }
 __device__ __forceinline__ float to_float(uint16_t v) { return bf2f(v); }
 
 // ---- the same for rows that start on any element -----------------------------
-// Eight consecutive elements with only element alignment: the hardware takes
+// Four consecutive elements with only element alignment: the hardware takes 8 and
 // 16-byte global accesses at any address (a wave's span just touches one more
 // line), so a row needs no peeling to a 16-byte boundary.
 typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
-typedef unsigned u32x4u_t __attribute__((ext_vector_type(4), aligned(2)));
+typedef unsigned u32x2u_t __attribute__((ext_vector_type(2), aligned(2)));
 
-template <typename T> struct RowIO {
-  __device__ __forceinline__ static void get4(const float* p, float v[4]) {
-    const f32x4u_t x = __builtin_nontemporal_load((const PRM_GLOBAL f32x4u_t*)p);
+template <typename T> struct RowIO;
+
+template <> struct RowIO<float> {
+  using Raw = f32x4u_t;  // four elements as stored, for expand once the loads have been issued
+  __device__ __forceinline__ static Raw load4(const float* p) {
+    return __builtin_nontemporal_load((const PRM_GLOBAL Raw*)p);
+  }
+  __device__ __forceinline__ static void expand(Raw x, float v[4]) {
     v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
   }
-  __device__ __forceinline__ static void put4(float* p, const float v[4]) {
-    const f32x4u_t x = {v[0], v[1], v[2], v[3]};
-    __builtin_nontemporal_store(x, (PRM_GLOBAL f32x4u_t*)p);
+  __device__ __forceinline__ static void store4(float* p, const float v[4]) {
+    const Raw x = {v[0], v[1], v[2], v[3]};
+    __builtin_nontemporal_store(x, (PRM_GLOBAL Raw*)p);
   }
-  __device__ __forceinline__ static void load8(const T* p, float v[8]) {
-    if constexpr (sizeof(T) == 2) {
-      const u32x4u_t x = __builtin_nontemporal_load((const PRM_GLOBAL u32x4u_t*)p);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        v[2 * k] = bf2f(x[k] & 0xffffu);
-        v[2 * k + 1] = bf2f(x[k] >> 16);
-      }
-    } else {
-      get4(p, v);
-      get4(p + 4, v + 4);
-    }
+};
+
+template <> struct RowIO<uint16_t> {
+  using Raw = u32x2u_t;
+  __device__ __forceinline__ static Raw load4(const uint16_t* p) {
+    return __builtin_nontemporal_load((const PRM_GLOBAL Raw*)p);
   }
-  __device__ __forceinline__ static void store8(T* p, const float v[8]) {
-    if constexpr (sizeof(T) == 2) {
-      const u32x4u_t x = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])};
-      __builtin_nontemporal_store(x, (PRM_GLOBAL u32x4u_t*)p);
-    } else {
-      put4(p, v);
-      put4(p + 4, v + 4);
-    }
+  __device__ __forceinline__ static void expand(Raw x, float v[4]) {
+    v[0] = bf2f(x[0] & 0xffffu); v[1] = bf2f(x[0] >> 16);
+    v[2] = bf2f(x[1] & 0xffffu); v[3] = bf2f(x[1] >> 16);
+  }
+  __device__ __forceinline__ static void store4(uint16_t* p, const float v[4]) {
+    const Raw x = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+    __builtin_nontemporal_store(x, (PRM_GLOBAL Raw*)p);
   }
 };
 

@@ -131,11 +131,14 @@ __device__ __forceinline__ void wide_row(const MatDesc& d, int64_t row, float* r
 }
 
 // Rows of any length and start, otherwise as above (TPR 64: a wave per row; 256:
-// a block per row).  One pass with 16-byte accesses instead of two sweeps of
+// a block per row).  One pass with four elements an access instead of two sweeps of
 // single elements; the last n % 8 elements are one each for the row's first
 // threads.  The sum of squares is the one of the two-sweep kernel below, bit for
 // bit: 256 partial sums over elements e, e + 256, ... (Kahan), for which the
-// elements change hands through LDS (`x`: 8 TPR floats of the row).
+// elements change hands through LDS (`x`: 8 TPR floats of the row).  HBM-bound; 60 M
+// elements in rows of 3001, us in two sweeps / eight elements of a thread side by
+// side, so that fp32 accesses left every other 16 bytes to the next one / now: 203 /
+// 233 / 185 in fp32, 179 / 151 / 138 in bf16 (fp32 momentum).
 template <int TPR, int NCH, DType WD, DType GD>
 __device__ __forceinline__ void ragged_row(const MatDesc& d, int64_t row, float* x, float* red, const RwParams& p) {
   using WT = typename Store<WD>::T;
@@ -154,18 +157,26 @@ __device__ __forceinline__ void ragged_row(const MatDesc& d, int64_t row, float*
   float* M = d.M + row * n;
   WT* W = reinterpret_cast<WT*>(d.W) + row * n;
 
-  float g[NCH][8], u[NCH][8], w[NCH][8];
-  bool ok[NCH];
+  // Chunk `it` of the row is 8 TPR elements, two pieces of 4 to a thread (h), so that
+  // every access is one span across the wave; gradients and weights stay as stored
+  // until they are used (converted under the branch, each load would be waited for).
+  typename RowIO<GT>::Raw g[NCH][2];
+  typename RowIO<WT>::Raw w[NCH][2];
+  float u[NCH][8];
+  bool ok[NCH][2];
+  auto at = [&](int it, int h) __attribute__((always_inline)) { return (int64_t)(2 * it + h) * (4 * TPR) + 4 * lt; };
 #pragma unroll
-  for (int it = 0; it < NCH; ++it) {
-    const int64_t e = (int64_t)(it * TPR + lt) * 8;
-    ok[it] = row_ok && e < n8;
-    if (ok[it]) {
-      RowIO<GT>::load8(G + e, g[it]);
-      RowIO<float>::load8(M + e, u[it]);
-      RowIO<WT>::load8(W + e, w[it]);
+  for (int it = 0; it < NCH; ++it)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t e = at(it, h);
+      ok[it][h] = row_ok && e < n8;
+      if (ok[it][h]) {
+        g[it][h] = RowIO<GT>::load4(G + e);
+        RowIO<float>::expand(RowIO<float>::load4(M + e), u[it] + 4 * h);
+        w[it][h] = RowIO<WT>::load4(W + e);
+      }
     }
-  }
   const int64_t et = n8 + lt;  // this thread's element of the row's ragged end
   const bool tail = row_ok && et < n;
   float gt = 0.f, ut = 0.f, wt = 0.f;
@@ -186,19 +197,22 @@ __device__ __forceinline__ void ragged_row(const MatDesc& d, int64_t row, float*
 #pragma unroll
   for (int it = 0; it < NCH; ++it) {
     if ((int64_t)it * TPR * 8 >= n8) break;  // the same for every thread of the row
-    if (ok[it]) {
-      const int64_t e = (int64_t)(it * TPR + lt) * 8;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) u[it][k] = new_momentum<GD, false>(u[it][k], g[it][k], p);
-      RowIO<float>::store8(M + e, u[it]);
-      if (p.nesterov) {
+    for (int h = 0; h < 2; ++h)
+      if (ok[it][h]) {
+        const int64_t e = at(it, h);
+        float* const v = u[it] + 4 * h;
+        float gv[4];
+        RowIO<GT>::expand(g[it][h], gv);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) u[it][k] = fmaf(p.beta, u[it][k], g[it][k]);
+        for (int k = 0; k < 4; ++k) v[k] = new_momentum<GD, false>(v[k], gv[k], p);
+        RowIO<float>::store4(M + e, v);
+        if (p.nesterov) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[k] = fmaf(p.beta, v[k], gv[k]);
+        }
+        *reinterpret_cast<f32x4_t*>(x + h * 4 * TPR + 4 * lt) = f32x4_t{v[0], v[1], v[2], v[3]};
       }
-      f32x4_t* const mine = reinterpret_cast<f32x4_t*>(x + 8 * lt);
-      mine[0] = f32x4_t{u[it][0], u[it][1], u[it][2], u[it][3]};
-      mine[1] = f32x4_t{u[it][4], u[it][5], u[it][6], u[it][7]};
-    }
     exchange();
     // elements it * 8 TPR + 256 k + (partial sum's number)
 #pragma unroll
@@ -234,19 +248,21 @@ __device__ __forceinline__ void ragged_row(const MatDesc& d, int64_t row, float*
   const float kcoef = p.gamma * d.s * (1.0f / nu);
   float* const Dp = (p.write_d && d.D) ? d.D + row * n : nullptr;
 #pragma unroll
-  for (int it = 0; it < NCH; ++it) {
-    if (ok[it]) {
-      const int64_t e = (int64_t)(it * TPR + lt) * 8;
-      float dv[8];
+  for (int it = 0; it < NCH; ++it)
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        dv[k] = u[it][k] * kcoef;
-        w[it][k] = new_weight<WD, false>(w[it][k], dv[k], p);
+    for (int h = 0; h < 2; ++h)
+      if (ok[it][h]) {
+        const int64_t e = at(it, h);
+        float v[4], dv[4];
+        RowIO<WT>::expand(w[it][h], v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          dv[k] = u[it][4 * h + k] * kcoef;
+          v[k] = new_weight<WD, false>(v[k], dv[k], p);
+        }
+        RowIO<WT>::store4(W + e, v);
+        if (Dp) RowIO<float>::store4(Dp + e, dv);
       }
-      RowIO<WT>::store8(W + e, w[it]);
-      if (Dp) RowIO<float>::store8(Dp + e, dv);
-    }
-  }
   if (tail) {
     const float dv = ut * kcoef;
     VecNT<WT>::store1(W + et, new_weight<WD, false>(wt, dv, p));

@@ -67,3 +67,10 @@ def test_rows_of_the_refresh_prologue(assembly, kernel):
 def test_rows_of_aligned_tall_matrices_with_nesterov(assembly):
     kernel = "rw_tall_apply_kernelILNS_5DTypeE0ELS1_0ELb1ELb1ELb0ELi16E"
     assert in_flight(assembly("rowwise.hip"), kernel, "global_load_dwordx4") >= 20
+
+
+# ragged rows, a block of 256 threads with four chunks of 8 elements per thread
+@pytest.mark.parametrize("types", ["1ELS1_1", "1ELS1_0", "0ELS1_1", "0ELS1_0"])
+def test_pieces_of_ragged_rows(assembly, types):
+    kernel = f"rw_wide_kernelILi256ELi256ELi4ELNS_5DTypeE{types}ELb0E"
+    assert in_flight(assembly("rowwise.hip"), kernel, "global_load_dwordx4") >= 20
