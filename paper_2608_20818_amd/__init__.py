@@ -256,7 +256,7 @@ class Optimizer:
         self._want = {dt: _Tensors(self.shapes, dt, True) for dt in {F32, self.cfg.param_dtype, self.cfg.grad_dtype}}
 
     def _pointers(self, xs, dtype, what):
-        a = self._want[dtype].pointers(xs)
+        a = self._want[dtype].pointers(xs) if dtype in self._want else None  # cfg is the caller's to change
         if a is None:
             self._check_tensors(xs, _DT[dtype], what)
             skip = what == "directions"  # a matrix whose direction is not wanted
@@ -356,7 +356,7 @@ class AuxAdamW:
         self._want = {dt: _Tensors(self.numels, dt, False) for dt in {F32, self.cfg.param_dtype, self.cfg.grad_dtype}}
 
     def _pointers(self, xs, dtype, what):
-        a = self._want[dtype].pointers(xs)
+        a = self._want[dtype].pointers(xs) if dtype in self._want else None  # cfg is the caller's to change
         if a is None:
             self._check_tensors(xs, _DT[dtype], what)
             a = (ctypes.c_void_p * max(len(self.numels), 1))(*[0 if x is None else _ptr(x) for x in xs])

@@ -81,3 +81,26 @@ def test_native_checks_take_and_refuse_what_the_python_ones_do():
         with pytest.raises(Exception):
             torch.vmap(under_vmap)(torch.ones(2, 8, 16, device="cuda"))
     torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")
+def test_a_configuration_changed_after_construction_is_checked_as_it_stands():
+    """A caller may reuse its config object for another context: the storage types it
+    then names are held against the tensors, and raw pointers pass."""
+    cfg = prm.config_default(K=2, param_dtype=prm.F32, grad_dtype=prm.F32)
+    W, G, M = ([torch.zeros(s, device="cuda") for s in SHAPES] for _ in range(3))
+    with prm.Optimizer(SHAPES, cfg) as opt:
+        cfg.param_dtype = cfg.grad_dtype = prm.BF16
+        with pytest.raises(ValueError, match="bfloat16"):
+            opt.step(W, G, M, 1)
+        assert opt.step(*([x.data_ptr() for x in t] for t in (W, G, M)), 1) == 0
+    acfg = prm.adamw_config_default(param_dtype=prm.F32, grad_dtype=prm.F32)
+    flat = [torch.zeros(64, device="cuda") for _ in range(4)]
+    with prm.AuxAdamW([64], acfg) as aux:
+        acfg.param_dtype = prm.BF16
+        with pytest.raises(ValueError, match="bfloat16"):
+            aux.step(*([x] for x in flat), 1)
+        aux.step(*([x.data_ptr()] for x in flat), 1)
+    torch.cuda.synchronize()
+
