@@ -78,14 +78,23 @@ MARSHAL_LIB = os.path.join(HERE, "_marshal.so")
 
 def build_marshal() -> str:
     """The binding's native tensor checks (g++, torch's C++ headers, no device
-    code): csrc/marshal.cpp -> _marshal.so, a CPython module."""
+    code): csrc/marshal.cpp -> _marshal.so, a CPython module.  The library and the
+    binding work without it (the checks then run in Python), so where torch, its
+    headers or Python's are missing nothing is built and "" returned."""
     import sysconfig
 
-    import torch
-
+    try:
+        import torch
+    except ImportError:
+        print("_marshal.so not built: no torch", file=sys.stderr)
+        return ""
     root = os.path.dirname(torch.__file__)
     inc = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
            sysconfig.get_paths()["include"]]
+    for need in (os.path.join(inc[0], "torch", "csrc", "autograd", "python_variable.h"), os.path.join(inc[2], "Python.h")):
+        if not os.path.exists(need):
+            print(f"_marshal.so not built: no {need}", file=sys.stderr)
+            return ""
     tmp = MARSHAL_LIB + ".tmp"
     cmd = [shutil.which("g++") or "g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *[f"-I{i}" for i in inc], MARSHAL_SRC,
