@@ -231,7 +231,7 @@ __global__ __launch_bounds__(small::NTHREADS) void ns_small_kernel(const MatDesc
   // every wave reaches once it has read stage s - 1 (whose buffer it takes).
   // While the previous stage's products run from one register set, the stage's
   // fragments are read into the other and the loads are issued, spread between
-  // the products: one wave per SIMD has nothing else to hide them behind.
+  // the products: the two waves of a SIMD have little else to hide them behind.
   // NP = 3 (`tri`): the two fragment sets are hi and lo of one k-step, and the
   // products hi hi, hi lo and lo hi; otherwise they are the group's two k-steps.
   auto main_loop = [&](auto rd_a, auto rd_b, auto npc) __attribute__((always_inline)) {

@@ -323,6 +323,12 @@ int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const pr
   for (int i = 0; i < n_mats; ++i) {
     P.rp.push_back(round_up(std::min(P.m[i], P.nn[i]), P.tile));
     P.cp.push_back(round_up(std::max(P.m[i], P.nn[i]), P.tile));
+    // on small tiles the factored form's fifth split matrix, rp x rp bf16 and rp fp32,
+    // lies over an iterate: R x C bf16 with R >= rp and C >= rp + 2, as C is at least
+    // 256 and rp at most 128, or r > 128 and c >= 2r >= r + 129 >= rp + 2
+    if (P.chain[i] && P.tile != kNsTile &&
+        (uint64_t)P.rp[i] * P.rp[i] * 2 + (uint64_t)P.rp[i] * 4 > NsRegions(P.rp[i], P.cp[i]).iterate)
+      return fail(PRM_EHIP, "internal: matrix %d has no room for its fifth split matrix", i);
   }
   // ---- small persistent buffers: prologue partial sums + alpha per matrix ----
   uint64_t off = 0;
@@ -720,8 +726,7 @@ void fill_descs(const Plan& P, char* chunk_base, char* small_base, char* tall_ba
       d.S[k] = k < ns ? (uint16_t*)(w + nx * xs + k * gs) : nullptr;
       d.dS[k] = k < ns ? (float*)(w + nx * xs + ns * gs + k * vs) : nullptr;
     }
-    // the factored form needs a fifth split matrix on small tiles; rp x rp bf16
-    // and rp fp32 fit an iterate's region: cp > rp, or both are 64 in one of 256 x 256
+    // the factored form needs a fifth split matrix on small tiles (make_plan: it fits)
     const bool fifth = P.chain[i] && P.tile != kNsTile;
     d.S[4] = fifth ? d.XT : nullptr;
     d.dS[4] = fifth ? (float*)(d.XT + d.rp * d.rp) : nullptr;

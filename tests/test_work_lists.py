@@ -134,3 +134,11 @@ def test_balanced_lists_where_they_save_time():
         f = max if kind == GRAM else min
         load = [sum(-(-f(shapes[m]) // t) for m, _, _ in items[x::8] if m >= 0) for x in range(8)]
         assert max(load) <= 1.03 * sum(load) / 8
+
+
+def test_small_tiles_have_room_for_the_fifth_split_matrix():
+    # factored form around every tile edge and both sides of its aspect ratio
+    cfg = prm.config_default()
+    for r in range(1, 700):
+        for c in (2 * r, 2 * r + 1, 2 * r + 63, 3 * r):
+            assert prm.plan_workspace_bytes([(r, c)], cfg) > 0
