@@ -294,8 +294,9 @@ void choose_tile(Plan& P) {
   }
 }
 
+// `tile`: the tile edge to plan for (tests), 0 for choose_tile's.
 int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const prm_config* cfg,
-              Plan& P) {
+              Plan& P, int tile = 0) {
   int rc = validate_cfg(cfg);
   if (rc) return rc;
   if (n_mats < 0) return fail(PRM_EINVAL, "n_mats must be >= 0");
@@ -319,7 +320,8 @@ int make_plan(int32_t n_mats, const int64_t* rows, const int64_t* cols, const pr
     P.chain.push_back(!cfg->ns_plain && !cfg->ns_precise && c >= 2 * r ? 1 : 0);
     P.s.push_back(shape_scale(m, n, cfg->scale_mode));
   }
-  choose_tile(P);
+  if (tile) P.tile = tile;
+  else choose_tile(P);
   for (int i = 0; i < n_mats; ++i) {
     P.rp.push_back(round_up(std::min(P.m[i], P.nn[i]), P.tile));
     P.cp.push_back(round_up(std::max(P.m[i], P.nn[i]), P.tile));
@@ -1207,8 +1209,8 @@ int noalloc_scratch(int dev, char** out) {
 }
 
 // Plan and layout of step `step` of one matrix.
-int noalloc_plan(const prm_config* cfg, int64_t rows, int64_t cols, int64_t step, Plan& P, NoallocLayout& L) {
-  const int rc = make_plan(1, &rows, &cols, cfg, P);  // prm_init's, so the same bits
+int noalloc_plan(const prm_config* cfg, int64_t rows, int64_t cols, int64_t step, Plan& P, NoallocLayout& L, int tile = 0) {
+  const int rc = make_plan(1, &rows, &cols, cfg, P, tile);  // prm_init's, so the same bits
   if (rc == PRM_OK) L = NoallocLayout(P, refresh_of(*cfg, step));
   return rc;
 }
@@ -1308,12 +1310,13 @@ int prm_plan_workspace_bytes(int32_t n_mats, const int64_t* rows, const int64_t*
   return PRM_OK;
 }
 
-int prm_init(prm_ctx** out, int32_t n_mats, const int64_t* rows, const int64_t* cols,
-             const prm_config* cfg, void* hip_stream) {
+// prm_init; `tile`: see make_plan.
+int prm_internal_init(prm_ctx** out, int32_t n_mats, const int64_t* rows, const int64_t* cols,
+                      const prm_config* cfg, void* hip_stream, int32_t tile) {
   if (!out) return fail(PRM_EINVAL, "out is NULL");
   *out = nullptr;
   prm_ctx* c = new prm_ctx();
-  int rc = make_plan(n_mats, rows, cols, cfg, c->plan);
+  int rc = make_plan(n_mats, rows, cols, cfg, c->plan, tile);
   if (rc) {
     delete c;
     return rc;
@@ -1355,6 +1358,11 @@ int prm_init(prm_ctx** out, int32_t n_mats, const int64_t* rows, const int64_t* 
   if (e != hipSuccess) return cleanup(fail(PRM_EHIP, "hipStreamSynchronize failed: %s", hipGetErrorString(e)));
   *out = c;
   return PRM_OK;
+}
+
+int prm_init(prm_ctx** out, int32_t n_mats, const int64_t* rows, const int64_t* cols,
+             const prm_config* cfg, void* hip_stream) {
+  return prm_internal_init(out, n_mats, rows, cols, cfg, hip_stream, 0);
 }
 
 int prm_step(prm_ctx* ctx, void* const* params, const void* const* grads, float* const* momentum,
@@ -1643,8 +1651,9 @@ int prm_peak_hbm(void* hip_stream, uint64_t bytes, double* read_gbs, double* wri
   return rc;
 }
 
-int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* param, const void* grad,
-                     float* momentum, int64_t step, float lr, int32_t* did_refresh, void* hip_stream) {
+// prm_step_noalloc; `tile`: see make_plan.
+int prm_internal_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* param, const void* grad, float* momentum,
+                              int64_t step, float lr, int32_t* did_refresh, void* hip_stream, int32_t tile) {
   if (!cfg) return fail(PRM_EINVAL, "cfg is NULL");
   if (step < 0) return fail(PRM_EINVAL, "step must be >= 0 (got %lld)", (long long)step);
   if (cfg->ns_precise) return fail(PRM_EINVAL, "ns_precise is not available in the allocation-free step");
@@ -1655,7 +1664,7 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   c2.workspace_budget_bytes = 1ull << 62;
   Plan P;
   NoallocLayout L;
-  int rc = noalloc_plan(&c2, rows, cols, step, P, L);
+  int rc = noalloc_plan(&c2, rows, cols, step, P, L, tile);
   if (rc) return rc;
   const void* ps[3] = {param, grad, momentum};
   for (int k = 0; k < 3; ++k) {
@@ -1730,9 +1739,15 @@ int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* pa
   return rho ? refresh_step(&c, eta, false) : rowwise_step(&c, eta, false);
 }
 
+int prm_step_noalloc(const prm_config* cfg, int64_t rows, int64_t cols, void* param, const void* grad,
+                     float* momentum, int64_t step, float lr, int32_t* did_refresh, void* hip_stream) {
+  return prm_internal_step_noalloc(cfg, rows, cols, param, grad, momentum, step, lr, did_refresh, hip_stream, 0);
+}
+
 const char* prm_last_error(void) { return g_err.c_str(); }
 
-// Access for the tests, not part of the C ABI (no declaration in prm.h).
+// Access for the tests, as prm_internal_init and prm_internal_step_noalloc above: not
+// part of the C ABI (no declaration in prm.h).
 //
 // What the allocation-free step of this shape would do, without a device: 1 if its
 // scratch fits the limit, 0 if it is refused; out: tile edge, bytes held against

@@ -3,6 +3,8 @@ inputs and measure the differences.  Inputs come from ``synth`` only; expected
 values come from ``oracle`` only."""
 from __future__ import annotations
 
+import contextlib
+import ctypes
 import math
 
 import numpy as np
@@ -117,3 +119,44 @@ def row_errors(A, B):
     num = np.linalg.norm(A - B, axis=1)
     den = np.maximum(np.linalg.norm(B, axis=1), 1e-300)
     return num / den
+
+
+class _TileLib:
+    """libprm with the tests' entry points in place of those that choose a tile."""
+
+    def __init__(self, real, tile):
+        self._real, self._tile = real, tile
+        for name, public in (("prm_internal_init", "prm_init"), ("prm_internal_step_noalloc", "prm_step_noalloc")):
+            f = getattr(real, name)
+            f.argtypes = [*getattr(real, public).argtypes, ctypes.c_int32]
+
+    def __getattr__(self, name):
+        return getattr(self._real, name)
+
+    def prm_init(self, *args):
+        return self._real.prm_internal_init(*args, self._tile)
+
+    def prm_step_noalloc(self, *args):
+        return self._real.prm_internal_step_noalloc(*args, self._tile)
+
+
+@contextlib.contextmanager
+def forced_tile(tile):
+    """Contexts made and allocation-free steps taken inside plan their NS5 products on
+    tiles of that edge (64, 128, 256) instead of the planner's choice."""
+    import paper_2608_20818_amd as prm
+    real = prm.load()
+    prm._lib = _TileLib(real, tile)
+    try:
+        yield
+    finally:
+        prm._lib = real
+
+
+def square_flops(shapes, tile):
+    """FLOPs one launch of the square runs over the set: whole upper tiles."""
+    total = 0
+    for m, n in shapes:
+        t = -(-min(m, n) // tile)
+        total += t * (t + 1) // 2 * 2 * tile ** 3 * t
+    return total

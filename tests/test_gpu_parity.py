@@ -76,9 +76,10 @@ def test_ragged_shapes_all_paths(t, wdt, gdt, plain):
     check(res, rho, cfg, RAGGED, cfg.lr)
 
 
-# several 256 x 256 tiles per symmetric product with padding: tiles above the
-# diagonal and their mirrors (Gram, square), the fold stage pairs and the
-# transposed parameter write of the last apply
+# several tiles per symmetric product with padding: tiles above the diagonal and
+# their mirrors (Gram, square), the diagonal terms and the transposed parameter
+# write of the last apply.  (The planner takes 128 x 128 tiles here;
+# test_gpu_tiles.py runs such sets on every tile edge.)
 MULTI_TILE = [(700, 2000), (1536, 520), (600, 600), (1300, 1800)]
 
 
@@ -95,8 +96,8 @@ def test_multi_tile_symmetric_products(t, wdt, gdt, plain):
 @pytest.mark.parametrize("t,wdt,gdt", [(0, 1, 1), (0, 0, 0), (4, 0, 1)])
 def test_precise_mode_multi_tile(t, wdt, gdt):
     """ns_precise (hi + lo iterates) over several tiles with padding: the
-    Gram's three K segments, the apply's two with a fold stage pair in each,
-    the hi + lo write of the next iterate, and the parameter write."""
+    Gram's three products, the apply's two K segments, the hi + lo write of
+    the next iterate, and the parameter write."""
     cfg = prm.config_default(K=4, lr=0.02, wd=0.1, param_dtype=wdt, grad_dtype=gdt, ns_precise=1)
     rho, res = run_one_step(MULTI_TILE, cfg, t, workload_id=95)
     assert rho == 1

@@ -65,7 +65,8 @@ def test_small_tiles_against_the_oracle(tile, i, precise, wdt, gdt):
         Wo, Mo, Do, _ = po.step_matrix(w0, m0, g[0], 0, oc)
         eD = pc.rel(pc.to_host(D[k]), Do)
         print(f"  {shapes[k]} D err {eD:.2e}", flush=True)
-        assert eD <= pc.TOL_NS5
+        # precise: 2.5e-3 to 4e-3; without an iterate's low half these inputs show 7e-3 and more
+        assert eD <= (5e-3 if precise else pc.TOL_NS5)
         assert pc.rel(pc.to_host(M[k]), Mo) <= pc.TOL_M
         # W = decay W0 - lr D with the GPU's own D, rounded once to its type
         if wdt == prm.BF16:
@@ -75,6 +76,8 @@ def test_small_tiles_against_the_oracle(tile, i, precise, wdt, gdt):
             diff = np.abs((pc.to_host(W[k]) - Wo) + lr * (pc.to_host(D[k]) - Do))
             assert diff.max() <= 2.0 ** -22 * (np.abs(Wo).max() + lr * np.abs(Do).max())
         assert torch.equal(W[k], Wt[k]) and torch.equal(M[k], Mt[k])
+        # every product in a launch of its own: the same bits as shared launches
+        assert torch.equal(W[k], Wt2[k]) and torch.equal(M[k], Mt2[k])
 
 
 def test_small_gemm_assembly_keeps_m0_and_its_wait_state(tmp_path):
