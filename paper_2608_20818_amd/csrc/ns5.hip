@@ -213,7 +213,9 @@ __global__ __launch_bounds__(256) void ns_alpha_kernel(const MatDesc* __restrict
       for (int k = 0; k < B; ++k) s += v[k];
     }
   };
-  if (nt <= 4 * 256) sum(std::integral_constant<int, 4>{});  // a small matrix does not step through 32
+  // a small matrix does not step through 32 (2048 x 6144: the refresh 509 us, else 507)
+  if (nt <= 4 * 256) sum(std::integral_constant<int, 4>{});
+  else if (nt <= 12 * 256) sum(std::integral_constant<int, 12>{});
   else sum(std::integral_constant<int, 32>{});
   s = block_sum<256>(s, red);
   if (threadIdx.x == 0) *d.alpha = 1.0f / (sqrtf(s) + p.eps_ns);

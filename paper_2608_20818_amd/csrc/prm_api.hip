@@ -507,8 +507,12 @@ struct XcdLists {
     return end;
   }
 
-  // The preferred list, unless the other one ends 3% earlier.
+  // The preferred list, unless the other one ends 3% earlier (over 40 rounds of tiles
+  // the end is too little of it to count).
   std::vector<Item> choose(bool prefer_balanced) const {
+    size_t tiles = 0;
+    for (const auto& t : mats) tiles += t.items.size();
+    if (tiles > (size_t)40 * kXcds * price.per_xcd) return prefer_balanced ? balanced() : in_turn();
     std::vector<Item> a = in_turn(), b = balanced();
     const double ta = time(a), tb = time(b);
     return (prefer_balanced ? ta >= 0.97 * tb : tb < 0.97 * ta) ? b : a;
