@@ -176,7 +176,10 @@ int prm_plan_workspace_bytes(int32_t n_mats, const int64_t* rows, const int64_t*
 
 /* Per-kernel-class timing on the context's stream, for measurement.
  * prm_profile_enable(ctx, 1) makes later steps record a HIP event pair around
- * every kernel launch (on the same stream); prm_profile_read synchronizes the
+ * every kernel launch (on the same stream) and gives every class launches of its
+ * own: the first passes of a row-wise step and pairs of NS5 products on small tiles,
+ * which otherwise share launches, run one after the other, with the same bits, so the
+ * classes of a small set add up to more than its step takes unprofiled; prm_profile_read synchronizes the
  * stream and fills out[0 .. min(n, PRM_NUM_KERNEL_CLASSES)) with, per kernel
  * class, the launch count, total GPU milliseconds, and the algorithmic bytes
  * and FLOPs of those launches, then clears the counters.  Classes, in order:

@@ -256,12 +256,12 @@ constexpr TilePrice kTilePrice[3] = {{256, 1.17, 9.0, 32}, {128, 0.42, 5.0, 32},
 // is priced as all its tiles' time over 256 plus half the longest tile (the uneven
 // end), but no less than the longest.  At 256 the plain and the factored group have
 // launches of their own; on small tiles they are priced as sharing every one.
-// Measured refresh, us at 64 / 128 / 256, the choice first: six matrices with
-// r <= 256: 100 / 153 / 580; ten with r = 384 (three steps): 294 / 322 / 980;
-// seven with r <= 1001: 128: 550, 559 / 1500; five with r = 1024, precise: 128:
-// 1168, 1410 / 2430; one 2048 x 6144: 128: 522, 667 / 1060; 15 with r = 2048:
-// 256: 5700, 8831 / 6695; 25 with r = 768: 128: 1103, 1105 / 1471; 25 with r = 1600:
-// 256: 6269, though 128 took 5956.
+// Measured refresh in us, the chosen tile first: five matrices with r = 512 64: 157,
+// 128: 219, 256: 871; one 2048 x 6144 128: 504, 256: 1086; five with r = 1024, precise,
+// 128: 1099, 256: 2476; 30 with r = 768 128: 1162, 256: 1534; 15 with r = 2048 256:
+// 5600, 128: 6555.  Over 90 sets no choice was slower than 256; some that stay on 256
+// are faster on 128 (25 with r = 1600 256: 6165, 128: 5990; 15 with r = 1280 2173,
+// 1962; four 2900 x 2910 2877, 2602).
 void choose_tile(Plan& P) {
   constexpr double kCus = 256;
   double best = 0;
